@@ -17,7 +17,13 @@
 //               windows are then evaluated one cell per thread (carry scan,
 //               in-window integrals, Eq. (1) in fp64) and one wave per step
 //               runs the smoothing chain over the previous chunk.
-//   rebalance   one wave per scenario, lane = model: Eq. (2), regions,
+//   seg_net, tss_seg, chain_smooth
+//               the same with few traces: the windows of a trace in segments,
+//               a workgroup each, then one chain per trace.
+//   rebalance_ordered
+//               one workgroup per scenario: three waves prepare the order in
+//               which each tick tries receivers and donors, one decides.
+//   rebalance   with many scenarios, one wave per scenario, lane = model: Eq. (2), regions,
 //               cadence and the greedy receiver/donor moves, with ballots
 //               as candidate sets and DPP wave folds for argmin / argmax
 //               (lowest index on ties), so every decision is a scalar.
@@ -34,6 +40,7 @@
 #include <algorithm>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "tre.h"
@@ -111,12 +118,20 @@ struct StreamParams {
   const tre_scenario* sc;
   const uint32_t* sc_count;  // [trace] scenarios on the trace, or NULL
   const uint32_t* sc_first;  // [trace] the scenario when the count is 1
+  int32_t ctl_one;           // one trace with one scenario: replayed without the map above
   int32_t budget;
   tre_move* moves;
   uint32_t move_cap;
   uint32_t* n_moves;
   int32_t* r_final;
   int64_t* r_windows;
+  // the segmented path (few traces): a workgroup per (trace, segment of
+  // seg_w windows), raw ratios to memory for chain_smooth
+  int32_t nseg, seg_w;
+  const int32_t* seg_row;              // [trace][nseg + 1] first row of each segment, from the trace's first
+  const unsigned long long* seg_net;   // [trace][nseg][M] net changes (pack_net)
+  double* raw;                         // [trace][column][window], -1 marks an idle window
+  uint32_t* first;                     // [trace][column] first window that is not idle
 };
 
 // quotient and remainder of rel / window_ms for any 32-bit rel: the
@@ -260,7 +275,7 @@ __device__ __forceinline__ void tally_slice(const Slice<kEPT>& s, int c0, int a0
       const int w = cbase + (int)q;
       if (d >= cap) {
         jdef = j;
-        wdf = w;
+        wdf = w < cbase ? INT_MAX : w;  // before the ring: unsorted input only; the windows still complete
         go = false;
       } else {
         if (c0 + j == t_last) *wlast = w;
@@ -313,6 +328,20 @@ __device__ __forceinline__ void tally_fast(const Slice<kEPT>& s, uint32_t base_l
     tally_row(ring, __umul24((q + cbm) & wmask, sstride8) + (mdl << 5), ty, tok, te);
   }
   if (last) *wlast = cbase + (int)ql;
+}
+
+// A segment's net changes of one model's active and waiting counts as one
+// 64-bit sum of (dA << 32) + dW over its rows, dW of either sign; the halves
+// come apart again because |dA|, |dW| < 2^27.
+__device__ __forceinline__ int net_w(unsigned long long v) { return (int)(uint32_t)v; }
+__device__ __forceinline__ int net_a(unsigned long long v) {
+  return (int)(uint32_t)((v - (unsigned long long)(long long)net_w(v)) >> 32);
+}
+
+// x / d likewise
+__device__ __forceinline__ uint32_t div_magic(uint32_t x, uint32_t d, uint32_t magic) {
+  const uint32_t q = __umulhi(x, magic);
+  return q + (x - q * d >= d ? 1u : 0u);
 }
 
 // x mod d for x < 2^32, with magic = floor(2^32 / d) (2^32 - 1 for d = 1):
@@ -521,15 +550,6 @@ __device__ __forceinline__ void ctl_tick(CtlState& st, const CtlConst& c, int la
   }
 }
 
-// One model's replay constants and state in LDS, for a replay that moves
-// between waves from step to step.
-struct CtlModel {
-  double theta;     // theta * theta_scale
-  double tau_c, tau_s;
-  long long rw;
-  int R, since, r_min, pad;
-};
-
 // Initial replica state of a scenario (lane m = model m): R = r_init, idle
 // = budget - sum of g * r_init over the models.
 __device__ __forceinline__ void ctl_init(CtlState& st, int r_init, int g, bool act, int budget) {
@@ -551,6 +571,242 @@ __device__ __forceinline__ void ctl_init(CtlState& st, int r_init, int g, bool a
   st.tret = 0;
 }
 
+// ---- a tick's decisions prepared ahead of the replay
+// What a tick decides depends on the replica state only through who may
+// give and how much is idle; the order in which receivers and donors are
+// tried does not. So waves other than the replay's put both orders of each
+// tick into LDS (tick_order), several ticks at a time, and the replay's
+// serial part per move is bit scans on wave masks and one compare
+// (ctl_batch) instead of two or three wave-wide folds of 64-bit values:
+// 1024 replays of 720 ticks over 8 models, one wave each, took 0.53 ms with
+// the folds.
+//   recv[i]  the i-th receiver: models of the tick's path (critical, or Z <
+//            1), lowest Z first, lowest index on ties: model | rank << 8
+//   don[i]   the i-th donor: models not critical, surplus before the rest,
+//            highest Z first, lowest index on ties: model | rank << 8 |
+//            position among the receivers << 16 (64: not one)
+// with rank the number of models with a smaller Z (equal Z, equal rank), and
+// kNoModel past the last; head: window | path << 30, path 0 when no move can
+// follow.
+constexpr uint32_t kNoModel = 0xFFFFFFFFu;
+
+// Lanes in groups of G = 2^lg (the least power of two that holds M models),
+// one group per tick, sub-lane = model: Z of the lane's tick and model
+// (unused lanes of a tick, and lanes whose `in` is false, take no part).
+// recv, don, head: the lane's tick. zs: 64 words of LDS for this wave alone.
+__device__ __forceinline__ void tick_order(uint32_t* recv, uint32_t* don, uint32_t* head, unsigned long long* zs, int lane, int lg, int M,
+                                           bool in, double Z, double tau_c, double tau_s, uint32_t w, uint32_t kind) {
+  const int sub = lane & ((1 << lg) - 1), base = lane - sub;
+  const unsigned long long gm = (lg == 6 ? 0ull : 1ull << (1 << lg)) - 1ull;
+  auto group = [&](bool b) { return (__ballot(b) >> base) & gm; };
+  const bool act = in && sub < M;
+  const bool cr = act && Z < tau_c;
+  const bool crit = group(cr) != 0ull;
+  const bool ok = crit ? cr : (act && Z < 1.0);
+  const bool give = act && !cr, sur = Z > tau_s;
+  const unsigned long long okm = group(ok), givem = group(give), surm = group(give && sur);
+  uint32_t path = crit ? ((kind & 1u) ? TRE_PATH_RESCUE : 0u)  // rescue pending: rebalancing defers
+                       : ((kind & 2u) ? TRE_PATH_REBALANCE : 0u);
+  if (okm == 0ull) path = 0u;
+  if (in && sub == 0) *head = w | (path << 30);
+  if (!__ballot(in && path != 0u)) return;
+  uint32_t rank = 0, p = 0, q = 0;  // models with a smaller Z; receivers and donors before this lane's model
+  // Z >= 0 and never NaN, so its bit pattern orders like its value; zs holds
+  // the wave's own words (its LDS operations stay in order)
+  const unsigned long long zm = dbits(Z);
+  const uint32_t nsur = sur ? 0u : 1u;
+  zs[lane] = zm;
+  __builtin_amdgcn_wave_barrier();
+  auto count = [&](uint32_t okw, uint32_t givew, uint32_t surw, int j0, int n) {  // models j0 .. j0 + n - 1 (at most 32)
+#pragma unroll 4
+    for (int j = 0; j < n; ++j) {
+      const unsigned long long zj = zs[base + j0 + j];
+      const uint32_t less = zj < zm ? 1u : 0u, first = (j0 + j < sub ? zj <= zm : zj < zm) ? 1u : 0u;
+      const uint32_t above = (j0 + j < sub ? zj >= zm : zj > zm) ? 1u : 0u;
+      const uint32_t sj = __builtin_amdgcn_ubfe(surw, (uint32_t)j, 1);
+      rank += less;
+      p += __builtin_amdgcn_ubfe(okw, (uint32_t)j, 1) & first;
+      // a surplus model goes before every other, then the higher Z
+      q += __builtin_amdgcn_ubfe(givew, (uint32_t)j, 1) & ((sj & nsur) | ((sj ^ nsur) & above));
+    }
+  };
+  count((uint32_t)okm, (uint32_t)givem, (uint32_t)surm, 0, M < 32 ? M : 32);
+  if (M > 32) count((uint32_t)(okm >> 32), (uint32_t)(givem >> 32), (uint32_t)(surm >> 32), 32, M - 32);
+  if (act && path != 0u) {
+    const uint32_t word = (uint32_t)sub | (rank << 8);
+    if (ok) recv[p] = word;
+    if (sub >= __popcll(okm)) recv[sub] = kNoModel;
+    if (give) don[q] = word | ((ok ? p : 64u) << 16);
+    if (sub >= __popcll(givem)) don[sub] = kNoModel;
+  }
+}
+
+// Replica state of a replay of prepared ticks: lane m = model m; pool and nm
+// are the same in every lane.
+struct OrdState {
+  int R;         // routable replicas of the lane's model
+  long long rw;  // sum over all windows of R as it stands: a change at window w adds it times the windows after w
+  int pool;      // idle replicas (GPUs under the actuation model)
+  uint32_t nm;   // moves decided so far
+  int g;
+  int tkind, tuntil, tret;  // as CtlState
+};
+
+struct OrdConst {
+  int r_min;
+  uint32_t K;
+  bool act;
+  int32_t n_windows, wake_w, sleep_w;
+  tre_move* moves;
+  uint32_t move_cap;
+};
+
+template <bool kAct>
+__device__ __forceinline__ void ord_complete(OrdState& st, const OrdConst& c, int w) {
+  if constexpr (kAct) {
+    const bool done = st.tkind != 0 && st.tuntil < w;
+    if (done && st.tkind == 1) {
+      st.rw += c.n_windows - 1 - st.tuntil;
+      st.R += 1;
+    }
+    unsigned long long back = __ballot(done && st.tkind == 2 && st.tret > 0);
+    while (back) {
+      const int l = __ffsll((long long)back) - 1;
+      st.pool += __builtin_amdgcn_readlane(st.tret, l);
+      back &= back - 1ull;
+    }
+    if (done) st.tkind = 0;
+  }
+}
+
+// The prepared ticks [0, n) of a batch, in order (recv and don M entries a
+// tick), with the rules and results of ctl_tick. Ticks that can move nothing
+// are passed over 64 at a time, and a tick's entries are read while the one
+// before it is decided. Receivers are taken in ascending Z, so one is never
+// a donor of the same tick (a donor's Z lies above the receiver's); a donor
+// leaves the receivers by its position among them. gm: the models'
+// footprints in LDS (kAct); veto(i): the tick's mask.
+template <bool kAct, class Veto>
+__device__ __forceinline__ void ctl_batch(OrdState& st, const OrdConst& c, int lane, int M, int n,
+                                          const uint32_t* recv, const uint32_t* don, const uint32_t* head,
+                                          const int* gm, Veto veto) {
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const uint32_t h = i0 + lane < n ? head[i0 + lane] : 0u;
+    unsigned long long todo = __ballot((h >> 30) != 0u);
+    if (!todo) continue;
+    const int ml = lane < M ? lane : 0;
+    int i = __ffsll((long long)todo) - 1;
+    uint32_t rw = recv[(i0 + i) * M + ml], dw = don[(i0 + i) * M + ml];
+    while (todo) {
+      todo &= todo - 1ull;
+      const int nx = todo ? __ffsll((long long)todo) - 1 : i;
+      const uint32_t rn = recv[(i0 + nx) * M + ml], dn = don[(i0 + nx) * M + ml];
+      const uint32_t hd = (uint32_t)__builtin_amdgcn_readlane((int)h, i);
+      const int w = (int)(hd & 0x3FFFFFFFu);
+      ord_complete<kAct>(st, c, w);
+      // the candidates, in order, as wave masks
+      const unsigned long long busy = kAct ? __ballot(st.tkind != 0) : 0ull;
+      const unsigned long long can =
+          __ballot(c.act && st.R > c.r_min) & (kAct ? ~(busy | veto(i0 + i)) : ~0ull);
+      unsigned long long rc = __ballot(c.act && rw != kNoModel && !(kAct && ((busy >> (rw & 63u)) & 1ull)));
+      unsigned long long dc = __ballot(c.act && dw != kNoModel && ((can >> (dw & 63u)) & 1ull));
+      const uint32_t drank = (dw >> 8) & 0xFFu;
+      int gd = 1;
+      if constexpr (kAct) gd = gm[dw & 63u];
+      unsigned long long gain = 0ull, lose = 0ull, slept = 0ull;  // models: a replica more, one less; receivers of a slept one
+      uint32_t k = 0, mv = 0;  // moves of this tick (at most one per receiver), lane i: the i-th
+      while (k < c.K && rc) {
+        const uint32_t rr = (uint32_t)__builtin_amdgcn_readlane((int)rw, __ffsll((long long)rc) - 1);  // Eq. (3)
+        const uint32_t r = rr & 63u;
+        const int g_r = kAct ? __builtin_amdgcn_readlane(st.g, (int)r) : 1;
+        const bool pool = st.pool >= g_r;
+        const unsigned long long cd = dc & __ballot(drank > (rr >> 8) && (!kAct || st.pool >= g_r - gd));
+        if (!pool && !cd) break;
+        const int at = (__ffsll((long long)cd) - 1) & 63;
+        const uint32_t dd = pool ? (64u << 16) | TRE_DONOR_POOL : (uint32_t)__builtin_amdgcn_readlane((int)dw, at);
+        const uint32_t rp = dd >> 16;
+        const unsigned long long dbit = pool ? 0ull : 1ull << (dd & 63u);
+        dc &= ~(pool ? 0ull : 1ull << at);
+        rc &= rc - 1ull;
+        rc &= ~(rp < 64u ? 1ull << (rp & 63u) : 0ull);
+        lose |= dbit;
+        gain |= 1ull << r;
+        if constexpr (kAct) {
+          slept |= pool ? 0ull : 1ull << r;
+          const int short_by = pool ? g_r : g_r - __builtin_amdgcn_readlane(st.g, (int)(dd & 63u));
+          if ((dbit >> lane) & 1ull) st.tret = short_by < 0 ? -short_by : 0;
+          st.pool -= short_by > 0 ? short_by : 0;
+        } else {
+          st.pool -= pool ? 1 : 0;
+        }
+        mv = (uint32_t)lane == k ? (hd >> 30) | (r << 8) | ((dd & 0xFFu) << 16) : mv;
+        ++k;
+      }
+      if ((uint32_t)lane < k && st.nm + (uint32_t)lane < c.move_cap) {
+        tre_move m;
+        m.window = (uint32_t)w;
+        m.path = (uint8_t)mv;
+        m.receiver = (uint8_t)(mv >> 8);
+        m.donor = (uint8_t)(mv >> 16);
+        m.pad = 0;
+        c.moves[st.nm + (uint32_t)lane] = m;
+      }
+      st.nm += k;
+      // the routable changes: the donors' at once (from w + 1), the receivers'
+      // here only without the actuation model (else when their wakes complete)
+      const bool lost = (lose >> lane) & 1ull, got = (gain >> lane) & 1ull;
+      const int dR = (!kAct && got ? 1 : 0) - (lost ? 1 : 0);
+      st.R += dR;
+      st.rw += (long long)dR * (c.n_windows - 1 - w);
+      if constexpr (kAct) {
+        if (got) {
+          st.tkind = 1;
+          st.tuntil = w + c.wake_w + (((slept >> lane) & 1ull) ? c.sleep_w : 0);
+        }
+        if (lost) {
+          st.tkind = 2;
+          st.tuntil = w + c.sleep_w;
+        }
+      }
+      i = nx;
+      rw = rn;
+      dw = dn;
+    }
+  }
+}
+
+// the state before the first window, and the outputs after the last
+__device__ __forceinline__ void ord_init(OrdState& st, const OrdConst& c, int r_init, int g, int budget) {
+  CtlState s0;
+  ctl_init(s0, r_init, g, c.act, budget);
+  st.R = s0.R;
+  st.rw = (long long)s0.R * c.n_windows;
+  st.pool = s0.pool;
+  st.nm = 0;
+  st.g = g;
+  st.tkind = st.tuntil = st.tret = 0;
+}
+
+template <bool kAct>
+__device__ __forceinline__ void ord_finish(OrdState& st, const OrdConst& c, int lane, int32_t* r_final,
+                                           int64_t* r_windows, uint32_t* n_moves) {
+  ord_complete<kAct>(st, c, c.n_windows);  // transitions completing at the end of the last window count as done
+  if (c.act) {
+    r_final[lane] = st.R;
+    r_windows[lane] = st.rw;
+  }
+  if (lane == 0) *n_moves = st.nm;
+}
+
+// One model's replay constants and state in LDS, for a replay that moves
+// between waves from step to step.
+struct CtlModel {
+  double theta;     // theta * theta_scale
+  double tau_c, tau_s;
+  long long rw;
+  int R, since, r_min, pad;
+};
+
 // One workgroup per trace; every thread tallies and evaluates, one barrier
 // per step. Step k, with [cA, cB) the chunk evaluated in step k-1 and
 // [cB, cC), cC = min(wl, cB + C), the windows completed by earlier tiles
@@ -569,7 +825,12 @@ __device__ __forceinline__ void ctl_init(CtlState& st, int r_init, int g, bool a
 //     over the chunk, window integrals, Eq. (1) -> raw ratio, staged in LDS
 //     (two staging buffers, by step parity);
 //   -- barrier -- the tile's rows are in; windows < wl are complete.
-template <int kWaves, int kEPT, bool kCells, bool kStage>
+//
+// kSeg: the workgroup takes one segment of a trace's windows, [w_lo, w_hi),
+// and that segment's rows; its carries start from the net changes of the
+// segments before it, the raw ratios go to memory and chain_smooth smooths
+// them, so there is no chain, control replay or staging here.
+template <int kWaves, int kEPT, bool kCells, bool kStage, bool kSeg = false>
 __device__ __forceinline__ void stream_body(const StreamParams& p) {
   constexpr int kThreads = kWaves * 64;
   constexpr long long kTile = (long long)kThreads * kEPT;
@@ -582,8 +843,10 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
   __shared__ unsigned s_defer[3];
   __shared__ int s_wdef[3];
   __shared__ int s_wlast[3];  // window of the tile's last row
+  __shared__ uint32_t s_first[kSeg ? 2 * TRE_MAX_MODELS : 1];  // kSeg: per column, the first window not idle
 
-  const int trace = blockIdx.x;
+  const int trace = kSeg ? (int)(blockIdx.x / (unsigned)p.nseg) : (int)blockIdx.x;
+  const int seg = kSeg ? (int)(blockIdx.x % (unsigned)p.nseg) : 0;
   const int tid = threadIdx.x;
   const int M = p.M;
   const uint32_t wcap = p.wcap;
@@ -611,12 +874,20 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
   // its chunk and the chunk's first window
   CtlModel* const s_cm = (CtlModel*)(st_raw + 3 * C * M);
   uint32_t* const s_cmeta = (uint32_t*)(s_cm + M);  // [0] idle, [1] moves, [2+b] fast, [5+b] slow, [8+b] window
-  const long long e_begin = p.off[trace];
-  const long long e_end = p.off[trace + 1];
+  long long e_begin = p.off[trace];
+  long long e_end = p.off[trace + 1];
+  if constexpr (kSeg) {
+    const int32_t* const sr = p.seg_row + (int64_t)trace * (p.nseg + 1) + seg;
+    const int r0 = sr[0], r1 = sr[1];  // within the trace's rows; r0 <= r1 when they are sorted
+    e_end = e_begin + (r1 > r0 ? r1 : r0);
+    e_begin += r0;
+  }
   const long long win = p.window_ms;
   const uint32_t win32 = (uint32_t)win;
   const double dwin = (double)win;
-  const int nW = p.n_windows;
+  const int nWt = p.n_windows;  // windows of the trace
+  const int w_lo = kSeg ? seg * p.seg_w : 0;
+  const int nW = kSeg ? (w_lo + p.seg_w < nWt ? w_lo + p.seg_w : nWt) : nWt;  // one past this workgroup's last
   constexpr bool cells = kCells;
 
   for (int i = tid; i < nring; i += kThreads) ring[i] = 0ull;
@@ -646,7 +917,7 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
   }
   // smoothing chain: one wave per step (rotating), lane m owns model m; its
   // state lives in LDS between steps
-  if (tid < M) {
+  if (!kSeg && tid < M) {
     s_alpha[tid] = p.prof[(int64_t)trace * M + tid].alpha;
     s_S[tid] = 0.0;
     s_init[tid] = 0;
@@ -665,8 +936,9 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
   // written for a separate replay)
   int ctl_s = -1;
   uint32_t ctl_K = 0;
-  if constexpr (!kStage) {
-    if (p.sc_count && p.sc_count[trace] == 1u) ctl_s = (int)p.sc_first[trace];
+  if constexpr (!kStage && !kSeg) {
+    if (p.ctl_one) ctl_s = 0;
+    else if (p.sc_count && p.sc_count[trace] == 1u) ctl_s = (int)p.sc_first[trace];
   }
   ctl_s = __builtin_amdgcn_readfirstlane(ctl_s);
   if (ctl_s >= 0) {
@@ -751,7 +1023,7 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
   const long long brow = e_begin & ~(long long)(kEPT - 1);
   const int rend = (int)(e_end - brow);  // one past the trace's last row
   int e0 = (int)(e_begin - brow);        // first row not yet tallied
-  int cA = 0, cB = 0, wl = 0;
+  int cA = w_lo, cB = w_lo, wl = w_lo;
   TraceRsrc rs;
   rs.ts = rsrc(p.ts + brow, (long long)rend * 8);
   rs.model = rsrc(p.model + brow, rend);
@@ -761,10 +1033,24 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
   int held = 0;  // tile base held by the current buffer
   load_slice<kEPT>(buf0, rs, tid * kEPT);
   __syncthreads();
+  if constexpr (kSeg) {
+    for (int i = tid; i < (kStage ? 2 : 1) * M; i += kThreads) s_first[i] = kNoDefer;
+    // the carries: the net changes of the segments before this one
+    const unsigned long long* const net = p.seg_net + (int64_t)trace * p.nseg * M;
+    for (int i = tid; i < seg * M; i += kThreads) {
+      const unsigned long long v = net[i];
+      const int m = i % M;
+      if (v) {
+        atomicAdd(&s_carry[0][0][m], net_a(v));
+        atomicAdd(&s_carry[0][1][m], net_w(v));
+      }
+    }
+    __syncthreads();
+  }
 
   // one step; returns true when every window has been smoothed
   auto step = [&](Slice<kEPT>& cur, Slice<kEPT>& nxt, int k) -> bool {
-    if (cA >= nW) return true;
+    if ((kSeg ? cB : cA) >= nW) return true;
     const int b3 = k % 3;
     // ---- issue the loads of tile k+1 first (and of tile k again when the
     // prefetch missed it): with both buffers live from here on, nothing
@@ -774,7 +1060,7 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
     const int pref = a0 + (int)kTile;
     load_slice<kEPT>(nxt, rs, pref + tid * kEPT);  // zeros past the trace
     // ---- smooth [cA, cB) (staged last step); wave k mod kWaves, lanes < M
-    if (wave == k % kWaves && cB > cA) {
+    if (!kSeg && wave == k % kWaves && cB > cA) {
       // the whole workgroup waits for this wave at the step's barrier: let its
       // dependent chain issue ahead of the other waves on its SIMD
       __builtin_amdgcn_s_setprio(3);
@@ -979,7 +1265,11 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
           if (den < dwin) den = dwin;
           raw = num / den;
         }
-        if constexpr (!kStage) sr[rj * M + rm] = idle ? -1.0 : raw;
+        if constexpr (!kStage && !kSeg) sr[rj * M + rm] = idle ? -1.0 : raw;
+        if constexpr (!kStage && kSeg) {
+          p.raw[((int64_t)trace * M + rm) * nWt + w] = idle ? -1.0 : raw;
+          if (!idle && (uint32_t)w < s_first[rm]) atomicMin(&s_first[rm], (uint32_t)w);
+        }
         if constexpr (kStage) {
           // the two parts of Eq. (1), each with its one-request floor; a
           // stage is idle when its tokens and its demand integral are zero
@@ -997,11 +1287,19 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
             if (den < dwin) den = dwin;
             rd = num / den;
           }
-          st_p[(k % nbuf) * C * M + rj * M + rm] = rp;
-          st_d[(k % nbuf) * C * M + rj * M + rm] = rd;
+          if constexpr (kSeg) {
+            double* const rw = p.raw + ((int64_t)trace * M + rm) * 2 * nWt + w;
+            rw[0] = rp;
+            rw[nWt] = rd;
+            if (rp >= 0.0 && (uint32_t)w < s_first[2 * rm]) atomicMin(&s_first[2 * rm], (uint32_t)w);
+            if (rd >= 0.0 && (uint32_t)w < s_first[2 * rm + 1]) atomicMin(&s_first[2 * rm + 1], (uint32_t)w);
+          } else {
+            st_p[(k % nbuf) * C * M + rj * M + rm] = rp;
+            st_d[(k % nbuf) * C * M + rj * M + rm] = rd;
+          }
         }
         if (cells) {
-          const int64_t o = ((int64_t)trace * nW + w) * M + rm;
+          const int64_t o = ((int64_t)trace * nWt + w) * M + rm;
           if (p.prefill) p.prefill[o] = P;
           if (p.decode) p.decode[o] = Dt;
           if (p.a_int) p.a_int[o] = (long long)A0 * win + la32;
@@ -1070,6 +1368,11 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
       break;
     }
   }
+  if constexpr (kSeg) {  // the last step's barrier made every s_first visible
+    const int K = (kStage ? 2 : 1) * M;
+    for (int i = tid; i < K; i += kThreads)
+      if (s_first[i] != kNoDefer) atomicMin(&p.first[(int64_t)trace * K + i], s_first[i]);
+  }
   // the ticks of the last chunk, then the replay's outputs (the last step's
   // barrier made the chain's values visible)
   if (ctl_s >= 0 && wave == 0) {
@@ -1086,6 +1389,465 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
 template <int kWaves, int kEPT, bool kCells>
 __global__ __launch_bounds__(kWaves * 64) void tss_stream(StreamParams p) {
   stream_body<kWaves, kEPT, kCells, false>(p);
+}
+
+// ------------------------------------------------------- segmented path
+// With few traces one workgroup per trace leaves most of the chip idle and
+// pays the smoothing chain, the evaluation and the tally in turn at every
+// step. There the windows of each trace are cut into segments:
+//   seg_net       per (trace, segment): its rows by binary search in the
+//                 sorted timestamps, and its net changes of the active and
+//                 waiting counts per model;
+//   tss_seg       per (trace, segment): stream_body with kSeg;
+//   chain_smooth  per trace: the smoothing chain over the raw ratios, the
+//                 per-cell outputs, the tick snapshot and, for a trace with
+//                 one scenario, the control replay.
+struct SegNetParams {
+  const int64_t* ts;
+  const uint8_t* model;
+  const uint8_t* type;
+  const int64_t* off;
+  int64_t window_ms;
+  int32_t n_windows, M, nseg, seg_w;
+  int32_t* seg_row;             // [trace][nseg + 1]
+  unsigned long long* seg_net;  // [trace][nseg][M]
+  uint32_t* first;              // [trace][K], set to "none" here
+  int32_t K;
+};
+
+// first row in [0, n) whose timestamp is at or above t (n if none): the whole
+// wave probes 64 rows a round, so a trace of 2^21 rows takes four rounds of
+// one load latency instead of 21. Unsorted input gives some row of [0, n].
+__device__ __forceinline__ int wave_lower_bound(const int64_t* ts, int n, int64_t t, int lane) {
+  int lo = 0, len = n;  // the answer lies in [lo, lo + len]
+  while (len > 0) {
+    const int stp = (len + 64) / 65;  // probes lo + stp * (lane + 1) - 1, at most 64 of them inside
+    const int at = lo + stp * (lane + 1) - 1;
+    const bool below = at < lo + len && ts[at] < t;
+    const int c = __popcll(__ballot(below));  // probes below t (a prefix when sorted)
+    const int nlo = lo + stp * c;
+    const int end = lo + stp * (c + 1) - 1;  // the first probe not below, or past the range
+    const int nend = c < 64 && end < lo + len ? end : lo + len;
+    len = nend > nlo ? nend - nlo : 0;
+    lo = nlo;
+  }
+  return lo < n ? lo : n;
+}
+
+constexpr int kNetThreads = 256;
+
+// bound by latency (the search's dependent probes) on short segments, by the
+// 2 bytes per row on long ones; a row costs one LDS add only if it changes a
+// count (about three in eleven)
+__global__ __launch_bounds__(kNetThreads) void seg_net(SegNetParams p) {
+  __shared__ unsigned long long s_net[4][TRE_MAX_MODELS];  // one copy per wave: fewer adds meet on one word
+  __shared__ int s_row[2];
+  const int trace = (int)(blockIdx.x / (unsigned)p.nseg), seg = (int)(blockIdx.x % (unsigned)p.nseg);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t b = p.off[trace], e = p.off[trace + 1];
+  const int n = (int)(e - b);
+  for (int i = tid; i < 4 * TRE_MAX_MODELS; i += kNetThreads) (&s_net[0][0])[i] = 0ull;
+  if (wave < 2) {  // wave 0: the first row, wave 1: the end
+    const int sg = seg + wave;
+    int r = sg == 0 ? 0 : n;
+    if (sg > 0 && sg < p.nseg) r = wave_lower_bound(p.ts + b, n, (int64_t)sg * p.seg_w * p.window_ms, lane);
+    if (lane == 0) s_row[wave] = r;
+  }
+  if (seg == 0)
+    for (int i = tid; i < p.K; i += kNetThreads) p.first[(int64_t)trace * p.K + i] = kNoDefer;
+  __syncthreads();
+  const int r0 = s_row[0], r1 = s_row[1] > r0 ? s_row[1] : r0;
+  if (tid == 0) {
+    // unsorted input may put a segment's first row after the next one's; each
+    // workgroup then reads rows [own first, next first) or none
+    int32_t* const sr = p.seg_row + (int64_t)trace * (p.nseg + 1);
+    sr[seg] = r0;
+    if (seg == p.nseg - 1) sr[p.nseg] = n;
+  }
+  // 16 rows per lane: 16-byte loads of the model and type bytes from the
+  // first 4-aligned row (buffer loads: past the range they read zeros)
+  const int64_t brow = (b + r0) & ~(int64_t)3;
+  const int skip = (int)(b + r0 - brow), rend = skip + (r1 - r0);
+  const __amdgpu_buffer_rsrc_t rm = rsrc(p.model + brow, rend), rt = rsrc(p.type + brow, rend);
+  unsigned long long* const net = s_net[wave];
+  const uint32_t mlast = (uint32_t)p.M - 1u;
+  v4u32 m4, t4, mn, tn;
+  m4 = __builtin_bit_cast(v4u32, __builtin_amdgcn_raw_buffer_load_b128(rm, tid * 16, 0, 0));
+  t4 = __builtin_bit_cast(v4u32, __builtin_amdgcn_raw_buffer_load_b128(rt, tid * 16, 0, 0));
+  for (int i0 = 0; i0 < rend; i0 += kNetThreads * 16) {
+    const int i = i0 + tid * 16;
+    mn = __builtin_bit_cast(v4u32, __builtin_amdgcn_raw_buffer_load_b128(rm, i + kNetThreads * 16, 0, 0));
+    tn = __builtin_bit_cast(v4u32, __builtin_amdgcn_raw_buffer_load_b128(rt, i + kNetThreads * 16, 0, 0));
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const uint32_t ty = (t4[j >> 2] >> (8 * (j & 3))) & 0xFFu;
+      const uint32_t code = (ty & 3u) | ((ty >> 5) & 4u);  // as tally_row: 0 ARRIVE, 3 FINISH, 5 ADMIT
+      if (((1u << code) & 0x29u) && i + j >= skip && i + j < rend) {
+        uint32_t mdl = (m4[j >> 2] >> (8 * (j & 3))) & 0xFFu;
+        mdl = mdl < mlast ? mdl : mlast;
+        // ARRIVE: dW + 1; ADMIT: dA + 1, dW - 1; FINISH: dA - 1
+        const unsigned long long d = code == 0u ? 1ull : code == 5u ? (1ull << 32) - 1ull : 0xFFFFFFFF00000000ull;
+        atomicAdd(&net[mdl], d);
+      }
+    }
+    m4 = mn;
+    t4 = tn;
+  }
+  __syncthreads();
+  if (tid < p.M)
+    p.seg_net[((int64_t)trace * p.nseg + seg) * p.M + tid] = s_net[0][tid] + s_net[1][tid] + s_net[2][tid] + s_net[3][tid];
+}
+
+template <int kWaves, int kEPT, bool kStage>
+__global__ __launch_bounds__(kWaves * 64) void tss_seg(StreamParams p) {
+  stream_body<kWaves, kEPT, !kStage, kStage, true>(p);
+}
+
+struct ChainParams {
+  const double* raw;       // [trace][column][window], -1 idle
+  const uint32_t* first;   // [trace][column]
+  const tre_profile* prof;
+  int32_t n_windows, M;
+  int32_t chunk_log2;      // windows per step: 2^chunk_log2, at least 8, chunk * columns <= kChainCells
+  int32_t stride;          // LDS words of 8 bytes per window: 9, 17, 33, 65 or 129
+  int32_t fast_w, slow_w, n_ticks;
+  uint32_t magic_fast, magic_slow, magic_both;  // floor(2^32 / d), 2^32 - 1 for 1
+  int32_t both_w;          // least common multiple of the two periods, or past the last window
+  uint32_t magic_k;        // floor(2^20 / columns) + 1: cell / columns for cells below 2^10
+  double* tss64;           // kStage: stage64
+  float* tss32;            // kStage: stage32
+  uint8_t* flags;
+  double* snap;
+  const uint32_t* tick_window;
+  const uint8_t* tick_kind;
+  // the control replay of a trace with one scenario
+  const tre_scenario* sc;
+  const uint32_t* sc_count;
+  const uint32_t* sc_first;
+  int32_t ctl_one;
+  int32_t budget;
+  tre_move* moves;
+  uint32_t move_cap;
+  uint32_t* n_moves;
+  int32_t* r_final;
+  int64_t* r_windows;
+};
+
+constexpr int kChainCells = 1024;       // cells per step
+constexpr int kChainWindows = 128;      // windows per step at most
+constexpr int kChainIO = 256;           // loading threads, and as many storing
+constexpr int kChainPer = kChainCells / kChainIO;
+constexpr int kChainRows = 16;          // columns up to which the chain runs in rows of 16 lanes
+// chain waves: four of four columns each, or a lane per column
+constexpr int chain_waves(bool rows) { return rows ? kChainRows / 4 : 2; }
+constexpr int chain_threads(bool rows) { return 64 * (chain_waves(rows) + 1) + 2 * kChainIO; }
+
+// S over C windows (a multiple of 8) of one column: S' = t1 + o * S with t1
+// and o of window u at t[u * kStr] and t[plane + u * kStr]; S' is written over
+// o. Two groups of windows in registers: the LDS reads of one (about 170
+// cycles) are in flight while the other's dependent multiplies and adds (12.4
+// cycles a window) run, and the stride is a constant, so that two windows
+// share one LDS instruction.
+template <int kStr>
+__device__ __forceinline__ double chain_run(double* t, int plane, int C, double S) {
+  constexpr int kG = 8;
+  double qt[kG], qo[kG], rt[kG], ro[kG];
+  double* o = t + plane;
+  auto read = [&](double (&x)[kG], double (&y)[kG], int at) {
+#pragma unroll
+    for (int u = 0; u < kG; ++u) x[u] = t[at + u * kStr];
+#pragma unroll
+    for (int u = 0; u < kG; ++u) y[u] = o[at + u * kStr];
+  };
+  auto run = [&](const double (&x)[kG], const double (&y)[kG]) {
+#pragma unroll
+    for (int u = 0; u < kG; ++u) {
+      const double t2 = y[u] * S;
+      S = x[u] + t2;
+      o[u * kStr] = S;
+    }
+    t += kG * kStr;
+    o += kG * kStr;
+  };
+  read(qt, qo, 0);
+  int u0 = 0;
+  for (; u0 + 2 * kG <= C; u0 += 2 * kG) {
+    read(rt, ro, kG * kStr);
+    run(qt, qo);
+    read(qt, qo, u0 + 2 * kG < C ? kG * kStr : 0);  // past the chunk: read, not used
+    run(rt, ro);
+  }
+  if (u0 < C) run(qt, qo);
+  return S;
+}
+
+// The same for up to four columns a wave, one row of 16 lanes each, lane u of
+// a row at window u0 + u of its column's plane: S moves one lane to the right
+// per window (DPP row_shr; lane 0 keeps the S of the row's last lane from the
+// block before). Every lane recomputes its own S at every step, and from step
+// u on lane u's is right. One LDS read of t1 and of o and one write of S per
+// 16 windows instead of 16 half-empty ones, whose cost does not fall with the
+// lanes in use: 25.9 cycles a window against 45 with a lane per column.
+__device__ __forceinline__ double chain_rows(double* t, int plane, int str, int C, double S) {
+  double t1 = t[0], o = t[plane];
+  for (int u0 = 0; u0 < C; u0 += 16) {
+    const int nx = u0 + 16 < C ? 16 * str : 0;
+    const double tn = t[nx], on = t[plane + nx];
+    auto lo = [](double x) { return (int)(uint32_t)dbits(x); };
+    auto hi = [](double x) { return (int)(uint32_t)(dbits(x) >> 32); };
+    auto of = [](int l, int h) { return __longlong_as_double((long long)(((unsigned long long)(uint32_t)h << 32) | (uint32_t)l)); };
+    int pl = __builtin_amdgcn_update_dpp(0, lo(S), 0x121, 0xF, 0xF, false);  // row_ror:1
+    int ph = __builtin_amdgcn_update_dpp(0, hi(S), 0x121, 0xF, 0xF, false);
+    double t2 = o * of(pl, ph);
+    S = t1 + t2;
+#pragma unroll
+    for (int u = 1; u < 16; ++u) {
+      pl = __builtin_amdgcn_update_dpp(pl, lo(S), 0x111, 0xF, 0xF, false);  // row_shr:1
+      ph = __builtin_amdgcn_update_dpp(ph, hi(S), 0x111, 0xF, 0xF, false);
+      t2 = o * of(pl, ph);
+      S = t1 + t2;
+    }
+    t[plane] = S;
+    t += nx;
+    t1 = tn;
+    o = on;
+  }
+  return S;
+}
+
+// One workgroup per trace, waves of four kinds that meet at one barrier per
+// step of `chunk` windows. A column is a model (kStage: a model's prefill or
+// decode share). In step k
+//   the loading waves put chunk k + 1 into LDS: per cell the t1 of S' = t1 +
+//     o * S, the smoothing of its window, and o: alpha * raw and 1 - alpha;
+//     raw at the column's first busy window, where S is still 0; -0.0 and 1
+//     at an idle one: the same binary64 operations on the same values as the
+//     documented order, and S itself where it is held. Their global loads run
+//     two chunks further ahead;
+//   the chain waves (kRows: a row of lanes per column, else a lane) run S over chunk k, one multiply and one
+//     add per window, writing S over o;
+//   the storing waves write the per-cell outputs of chunk k - 1, and prepare
+//     its ticks for the replay (or store them for a separate one);
+//   the control wave replays the ticks of chunk k - 2.
+// Bound by the dependent multiply-add of each window: everything else a
+// window needs is on other waves.
+template <bool kStage, bool kRows>
+__global__ __launch_bounds__(chain_threads(kRows), kRows ? 7 : 5) void chain_smooth(ChainParams p) {
+  constexpr int kChainWaves = chain_waves(kRows), kChainThreads = chain_threads(kRows);
+  extern __shared__ __align__(16) double cbuf[];  // [3][t1, then o and S][windows][stride]
+  __shared__ uint32_t s_first[2 * TRE_MAX_MODELS];
+  // the prepared ticks of a chunk (at most its windows), by step parity
+  __shared__ uint32_t s_recv[2][kStage ? 1 : kChainCells], s_don[2][kStage ? 1 : kChainCells];
+  __shared__ uint32_t s_head[2][kStage ? 1 : kChainWindows];
+  __shared__ unsigned long long s_z[kStage ? 1 : kChainIO / 64][64];
+  const int trace = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int M = p.M, K = kStage ? 2 * M : M, nW = p.n_windows;
+  const int lg = p.chunk_log2, C = 1 << lg;
+  const int str = p.stride;  // odd, so that a column's windows spread over the banks
+  const int plane = C * str, bufn = 2 * plane;
+  const int steps = (nW + C - 1) >> lg;
+  for (int i = tid; i < K; i += kChainThreads) s_first[i] = p.first[(int64_t)trace * K + i];
+  // the trace's one scenario, replayed here (else -1)
+  int ctl_s = -1;
+  if (!kStage) {
+    if (p.ctl_one) ctl_s = 0;
+    else if (p.sc_count && p.sc_count[trace] == 1u) ctl_s = (int)p.sc_first[trace];
+  }
+  ctl_s = __builtin_amdgcn_readfirstlane(ctl_s);
+  // ticks among the windows before w
+  auto ticks_before = [&](int w) {
+    return (int)(div_magic((uint32_t)w, (uint32_t)p.fast_w, p.magic_fast) +
+                 div_magic((uint32_t)w, (uint32_t)p.slow_w, p.magic_slow) -
+                 div_magic((uint32_t)w, (uint32_t)p.both_w, p.magic_both));
+  };
+  const bool act = lane < M;
+  const int m = act ? lane : 0;
+  __syncthreads();
+
+  if (wave >= kChainWaves + 1 && wave < kChainWaves + 1 + kChainIO / 64) {
+    // ---- loading waves
+    const int l = tid - 64 * (kChainWaves + 1);
+    double al[kChainPer], om[kChainPer];
+    int fst[kChainPer], dst[kChainPer], win[kChainPer];
+    const double* src[kChainPer];
+#pragma unroll
+    for (int j = 0; j < kChainPer; ++j) {
+      const int i = l + kChainIO * j, col = i >> lg, u = i & (C - 1);
+      const bool in = col < K;
+      al[j] = in ? p.prof[(int64_t)trace * M + (kStage ? col >> 1 : col)].alpha : 0.0;
+      om[j] = 1.0 - al[j];
+      fst[j] = in ? (int)s_first[col] - u : 0;  // the chunk's first window with which u is the first busy one
+      dst[j] = in ? u * str + col : -1;
+      win[j] = u;
+      src[j] = p.raw + ((int64_t)trace * K + (in ? col : 0)) * nW;
+    }
+    // no branch around a load, so that a wait covers only the older chunk's
+    auto load = [&](double (&v)[kChainPer], int k) {
+#pragma unroll
+      for (int j = 0; j < kChainPer; ++j) {
+        const int w = (k << lg) + win[j];
+        v[j] = src[j][w < nW ? w : nW - 1];
+      }
+    };
+    auto put = [&](const double (&v)[kChainPer], int k) {
+      double* const b = cbuf + (k % 3) * bufn;
+      const int w0 = k << lg;
+#pragma unroll
+      for (int j = 0; j < kChainPer; ++j) {
+        const bool idle = v[j] < 0.0;
+        const double a = al[j] * v[j];
+        if (dst[j] >= 0) {
+          b[dst[j]] = idle ? -0.0 : (w0 == fst[j] ? v[j] : a);
+          b[plane + dst[j]] = idle ? 1.0 : om[j];
+        }
+      }
+    };
+    double va[kChainPer], vb[kChainPer];
+    load(va, 0);
+    load(vb, 1);
+    put(va, 0);
+    load(va, 2);
+    __syncthreads();
+    for (int k = 0; k <= steps + 1; k += 2) {  // vb holds chunk k + 1, va chunk k + 2
+      if (k + 1 < steps) put(vb, k + 1);
+      load(vb, k + 3);
+      __syncthreads();
+      if (k > steps) break;
+      if (k + 2 < steps) put(va, k + 2);
+      load(va, k + 4);
+      __syncthreads();
+    }
+  } else if (wave < kChainWaves) {
+    // ---- chain waves
+    const int col = kRows ? wave * 4 + (lane >> 4) : tid;
+    const bool own = col < K;
+    double S = 0.0;
+    __builtin_amdgcn_s_setprio(3);
+    __syncthreads();
+    for (int k = 0; k <= steps + 1; ++k) {
+      double* const b = cbuf + (k % 3) * bufn + col;
+      if constexpr (kRows) {
+        if (k < steps && wave * 4 < K && own) S = chain_rows(b + (lane & 15) * str, plane, str, C, S);
+      } else if (k < steps && own) {
+        if (str == 33) S = chain_run<33>(b, plane, C, S);
+        else if (str == 65) S = chain_run<65>(b, plane, C, S);
+        else S = chain_run<129>(b, plane, C, S);
+      }
+      __syncthreads();
+    }
+    __builtin_amdgcn_s_setprio(0);
+  } else if (wave == kChainWaves) {
+    // ---- control wave: the prepared ticks of chunk k - 2
+    OrdState st{};
+    OrdConst c{};
+    c.n_windows = nW;
+    c.act = act;
+    if (ctl_s >= 0) {
+      const tre_profile pr = p.prof[(int64_t)trace * M + m];
+      c.r_min = pr.r_min;
+      c.K = (uint32_t)__builtin_amdgcn_readfirstlane((int)p.sc[ctl_s].max_moves);
+      c.moves = p.moves + (int64_t)ctl_s * p.move_cap;
+      c.move_cap = p.move_cap;
+      ord_init(st, c, pr.r_init, 1, p.budget);
+    }
+    __builtin_amdgcn_s_setprio(2);
+    __syncthreads();
+    for (int k = 0; k <= steps + 1; ++k) {
+      if (!kStage && k > 1 && ctl_s >= 0) {
+        const int w0 = (k - 2) << lg, we = w0 + C < nW ? w0 + C : nW;
+        ctl_batch<false>(st, c, lane, M, ticks_before(we) - ticks_before(w0), s_recv[k & 1], s_don[k & 1],
+                         s_head[k & 1], nullptr, [](int) { return 0ull; });
+      }
+      __syncthreads();
+    }
+    if (!kStage && ctl_s >= 0)
+      ord_finish<false>(st, c, lane, p.r_final + (int64_t)ctl_s * M, p.r_windows + (int64_t)ctl_s * M,
+                        p.n_moves + ctl_s);
+  } else {
+    // ---- storing waves: cells in output order, so that stores are contiguous
+    const int l = tid - 64 * (kChainWaves + 1) - kChainIO;
+    const bool vals = p.tss64 || p.tss32;
+    const int wv = wave - (kChainWaves + 1) - kChainIO / 64;  // storing wave
+    // ticks: lanes in groups of 2^lt, one group per tick, sub-lane = model
+    int lt = 0;
+    while ((1 << lt) < M) ++lt;
+    const int per = 64 >> lt, sub = lane & ((1 << lt) - 1);  // ticks a wave takes at once
+    const int ms = sub < M ? sub : 0;
+    const int fst = (int)s_first[kStage ? 0 : ms];
+    const bool ticks = !kStage && (ctl_s >= 0 || p.snap);
+    double th = 1.0, tau_c = 0.0, tau_s = 0.0;
+    if (!kStage && ctl_s >= 0) {
+      const tre_scenario sc = p.sc[ctl_s];
+      const tre_profile pr = p.prof[(int64_t)trace * M + ms];
+      th = pr.theta * sc.theta_scale;
+      tau_c = sc.tau_crit_override >= 0.0 ? sc.tau_crit_override : pr.tau_crit;
+      tau_s = pr.tau_surplus;
+    }
+    // the window and kind of tick `t`, clamped (read a step ahead)
+    auto tick_at = [&](int t) {
+      t = t < p.n_ticks ? t : p.n_ticks - 1;
+      return p.n_ticks > 0 ? p.tick_window[t] | ((uint32_t)p.tick_kind[t] << 30) : 0u;
+    };
+    const int mine = wv * per + (lane >> lt);  // this lane's tick among a round's
+    int t0 = 0;                                // ticks before the chunk
+    uint32_t twn = ticks ? tick_at(mine) : 0u;
+    __syncthreads();
+    for (int k = 0; k <= steps + 1; ++k) {
+      const int w0 = (k - 1) << lg;
+      const int n = w0 + C < nW ? C : nW - w0;
+      const double* const b = cbuf + ((k + 2) % 3) * bufn;  // chunk k - 1
+      if (ticks && k > 0 && k <= steps) {
+        const int nt = ticks_before(w0 + n) - t0;
+        uint32_t tw = twn;
+        twn = tick_at(t0 + nt + mine);
+        for (int i0 = 0; i0 < nt; i0 += 4 * per) {
+          const int i = i0 + mine;
+          if (i0) tw = tick_at(t0 + i);
+          const bool in = i < nt;
+          const int w = (int)(tw & 0x3FFFFFFFu);
+          const int u = in ? w - w0 : 0;
+          const double t1 = b[u * str + ms], Sw = b[plane + u * str + ms];
+          const bool dead = __double_as_longlong(t1) < 0 || w < fst || fst < 0;  // idle, or not initialised
+          if (ctl_s >= 0) {
+            const double Z = in && sub < M && !dead ? Sw / th : INFINITY;  // Eq. (2)
+            const int e = in ? i : 0;
+            tick_order(&s_recv[(k + 1) & 1][e * M], &s_don[(k + 1) & 1][e * M], &s_head[(k + 1) & 1][e], s_z[wv], lane, lt, M,
+                       in, Z, tau_c, tau_s, (uint32_t)w, tw >> 30);
+          } else if (in && sub < M) {
+            p.snap[((int64_t)trace * p.n_ticks + t0 + i) * M + sub] = dead ? INFINITY : Sw;
+          }
+        }
+        t0 += nt;
+      }
+      if (k > 0 && k <= steps && (vals || p.flags)) {
+        const int64_t o = ((int64_t)trace * nW + w0) * K;
+        for (int i = l; i < n * K; i += kChainIO) {
+          const int u = (int)(((uint32_t)i * p.magic_k) >> 20), col = i - u * K;
+          const double t1 = b[u * str + col], Sw = b[plane + u * str + col];
+          if (p.tss64) p.tss64[o + i] = Sw;
+          if (p.tss32) p.tss32[o + i] = (float)Sw;
+          if (!kStage && p.flags) {
+            const bool idle = __double_as_longlong(t1) < 0, init = (uint32_t)(w0 + u) >= s_first[col];
+            p.flags[o + i] = (uint8_t)((idle ? TRE_FLAG_IDLE : 0) | (init ? TRE_FLAG_INIT : 0));
+          }
+        }
+        if (kStage && p.flags) {
+          const int64_t of = ((int64_t)trace * nW + w0) * M;
+          for (int i = l; i < n * M; i += kChainIO) {
+            const int u = (int)(((uint32_t)(2 * i) * p.magic_k) >> 20), col = 2 * (i - u * M);
+            const bool pi = __double_as_longlong(b[u * str + col]) < 0, di = __double_as_longlong(b[u * str + col + 1]) < 0;
+            const uint32_t w = (uint32_t)(w0 + u);
+            p.flags[of + i] = (uint8_t)((pi ? TRE_STAGE_P_IDLE : 0) |
+                                        (w >= s_first[col] ? TRE_STAGE_P_INIT : 0) |
+                                        (di ? TRE_STAGE_D_IDLE : 0) |
+                                        (w >= s_first[col + 1] ? TRE_STAGE_D_INIT : 0));
+          }
+        }
+      }
+      __syncthreads();
+    }
+  }
 }
 
 // the stage-share instantiation, held to 80 VGPRs so that six workgroups
@@ -1214,6 +1976,124 @@ __global__ __launch_bounds__(256) void rebalance(CtlParams p) {
     p.r_windows[(int64_t)s * M + lane] = st.rw;
   }
   if (lane == 0) p.n_moves[s] = st.nm;
+}
+
+// The same replay with one workgroup per scenario: three waves prepare the
+// ticks of the next batch (tick_order) while the fourth decides those of the
+// one before it.
+constexpr int kOrdWaves = 3;
+constexpr int kOrdBatch = 8 * kOrdWaves;
+
+template <bool kAct>
+__global__ __launch_bounds__(64 * (kOrdWaves + 1)) void rebalance_ordered(CtlParams p) {
+  __shared__ uint32_t s_recv[2][kOrdBatch * TRE_MAX_MODELS], s_don[2][kOrdBatch * TRE_MAX_MODELS];
+  __shared__ uint32_t s_head[2][kOrdBatch];
+  __shared__ unsigned long long s_z[kOrdWaves][64];
+  __shared__ int s_g[TRE_MAX_MODELS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const uint32_t s = blockIdx.x;
+  const int M = p.M;
+  const tre_scenario sc = p.sc[s];
+  const uint32_t trace = sc.trace < p.n_traces ? sc.trace : 0;
+  if (p.sc_count && p.sc_count[trace] == 1u) return;  // replayed in the stream (whole workgroup)
+  const int nt = p.n_ticks;
+  const int nb = (nt + kOrdBatch - 1) / kOrdBatch;
+  if (wave == 0) {
+    const tre_profile pr = p.prof[(int64_t)trace * M + (lane < M ? lane : 0)];
+    OrdConst c;
+    c.r_min = pr.r_min;
+    c.K = (uint32_t)__builtin_amdgcn_readfirstlane((int)sc.max_moves);
+    c.act = lane < M;
+    c.n_windows = p.n_windows;
+    c.wake_w = p.wake_w;
+    c.sleep_w = p.sleep_w;
+    c.moves = p.moves + (int64_t)s * p.move_cap;
+    c.move_cap = p.move_cap;
+    int g = 1;
+    if (kAct && p.footprint && c.act) g = p.footprint[(int64_t)trace * M + lane];
+    s_g[lane] = g;  // read by this wave only
+    OrdState st;
+    ord_init(st, c, pr.r_init, g, p.budget);
+    // lane i: the vetoes of tick i of a batch, read a batch ahead
+    auto vetoes = [&](int b) {
+      const int t = b * kOrdBatch + lane;
+      return (kAct && p.veto && lane < kOrdBatch && t < nt) ? p.veto[(int64_t)trace * nt + t] : 0ull;
+    };
+    unsigned long long vt = 0, vn = vetoes(0);
+    __builtin_amdgcn_s_setprio(3);  // the workgroup waits for this wave
+    for (int b = 0; b <= nb; ++b) {
+      if (b > 0) {
+        const int t0 = (b - 1) * kOrdBatch;
+        ctl_batch<kAct>(st, c, lane, M, nt - t0 < kOrdBatch ? nt - t0 : kOrdBatch, s_recv[(b + 1) & 1],
+                        s_don[(b + 1) & 1], s_head[(b + 1) & 1], s_g, [&](int i) {
+                          if (!kAct) return 0ull;
+                          return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)vt, i) |
+                                 ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(vt >> 32), i) << 32);
+                        });
+      }
+      vt = vn;
+      vn = vetoes(b + 1);
+      __syncthreads();
+    }
+    ord_finish<kAct>(st, c, lane, p.r_final + (int64_t)s * M, p.r_windows + (int64_t)s * M, p.n_moves + s);
+  } else {
+    int lg = 0;
+    while ((1 << lg) < M) ++lg;
+    const int per = (64 >> lg) < 8 ? 64 >> lg : 8;  // ticks a wave takes at once, of its 8 per batch
+    const int sub = lane & ((1 << lg) - 1), tk = lane >> lg;
+    const int mc = sub < M ? sub : 0;
+    const tre_profile pr = p.prof[(int64_t)trace * M + mc];
+    const double theta_eff = pr.theta * sc.theta_scale;
+    const double tau_c = sc.tau_crit_override >= 0.0 ? sc.tau_crit_override : pr.tau_crit;
+    const int64_t tbase = (int64_t)trace * (p.flags ? p.n_windows : nt);
+    // round r of the wave: ticks at(r) + [0, per), one per lane group
+    const int rounds = 8 / per;
+    auto at = [&](int r) { return (r / rounds) * kOrdBatch + (wave - 1) * 8 + (r % rounds) * per + tk; };
+    // unconditional loads from clamped indices, a round (the tick's place in
+    // the log: two) ahead of their use
+    auto place = [&](int r) {
+      int t = at(r);
+      t = t < nt ? t : nt - 1;
+      return p.tick_window[t] | ((uint32_t)p.tick_kind[t] << 30);
+    };
+    auto value = [&](int r, uint32_t tw, uint32_t& f) {
+      int t = at(r);
+      t = t < nt ? t : nt - 1;
+      f = TRE_FLAG_INIT;
+      if (!p.flags) return p.vals[(tbase + t) * M + mc];
+      const int64_t cc = (tbase + (tw & 0x3FFFFFFFu)) * M + mc;
+      f = p.flags[cc];
+      return p.vals[cc];
+    };
+    uint32_t tw = 0, tn = 0, f = 0;
+    double v = 0.0;
+    if (nb > 0) {
+      tw = place(0);
+      tn = place(1);
+      v = value(0, tw, f);
+    }
+    for (int b = 0; b <= nb; ++b) {
+      if (b < nb) {
+        for (int r = b * rounds; r < (b + 1) * rounds; ++r) {
+          uint32_t fn;
+          const double vn = value(r + 1, tn, fn);
+          const uint32_t t2 = place(r + 2);
+          const bool live = sub < M && !(f & TRE_FLAG_IDLE) && (f & TRE_FLAG_INIT);
+          const double Z = live ? v / theta_eff : INFINITY;  // Eq. (2); +inf when idle or not initialised
+          const int t = at(r);
+          const bool in = t < nt && tk < per;
+          const int e = in ? t - b * kOrdBatch : 0;
+          tick_order(&s_recv[b & 1][e * M], &s_don[b & 1][e * M], &s_head[b & 1][e], s_z[wave - 1], lane, lg, M, in, Z,
+                     tau_c, pr.tau_surplus, tw & 0x3FFFFFFFu, tw >> 30);
+          v = vn;
+          f = fn;
+          tw = tn;
+          tn = t2;
+        }
+      }
+      __syncthreads();
+    }
+  }
 }
 
 // ---------------------------------------------------------------- validate
@@ -1480,6 +2360,78 @@ __global__ __launch_bounds__(256) void life_scan(LifeParams p) {
   }
 }
 
+// ------------------------------------------------ scratch of one call
+// The segmented path's scratch comes from a memory pool of the library's own
+// per device, allocated and freed in stream order, so that calls on several
+// streams or threads never share it. The pool keeps up to kPoolKeep bytes
+// between calls and gives everything back when the device's last handle is
+// freed. A stream that is being captured gets none (the caller then takes
+// the path that needs no scratch).
+constexpr uint64_t kPoolKeep = 512ull << 20;
+
+namespace {
+constexpr int kMaxDevices = 256;
+std::mutex g_pool_mu;
+hipMemPool_t g_pool[kMaxDevices];
+bool g_pool_tried[kMaxDevices];
+int g_handles[kMaxDevices];
+
+hipMemPool_t pool_for(int dev) {
+  if (dev < 0 || dev >= kMaxDevices) return nullptr;
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  if (!g_pool_tried[dev]) {
+    g_pool_tried[dev] = true;
+    hipMemPoolProps props{};
+    props.allocType = hipMemAllocationTypePinned;
+    props.location.type = hipMemLocationTypeDevice;
+    props.location.id = dev;
+    uint64_t keep = kPoolKeep;
+    hipMemPool_t pool = nullptr;
+    if (hipMemPoolCreate(&pool, &props) == hipSuccess &&
+        hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) == hipSuccess)
+      g_pool[dev] = pool;
+    (void)hipGetLastError();
+  }
+  return g_pool[dev];
+}
+
+void count_handle(int dev, int d) {
+  if (dev < 0 || dev >= kMaxDevices) return;
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  g_handles[dev] += d;
+  if (g_handles[dev] == 0 && g_pool[dev]) (void)hipMemPoolTrimTo(g_pool[dev], 0);
+}
+
+// `bytes` of scratch for work enqueued on `st`, or NULL
+class Scratch {
+ public:
+  Scratch(int dev, size_t bytes, hipStream_t st) : st_(st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return;
+    }
+    hipMemPool_t pool = pool_for(dev);
+    if (!pool) return;
+    if (hipMallocFromPoolAsync(&ptr_, bytes, pool, st) != hipSuccess) {
+      ptr_ = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  ~Scratch() {
+    if (ptr_) (void)hipFreeAsync(ptr_, st_);
+  }
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+  char* get() const { return (char*)ptr_; }
+
+ private:
+  void* ptr_ = nullptr;
+  hipStream_t st_;
+};
+
+}  // namespace
+
 // ------------------------------------------------------------------ timing
 namespace {
 struct Pending {
@@ -1589,6 +2541,23 @@ static int chunk_windows(int M, uint32_t wcap) {
 static int stream_waves(uint32_t n_traces) {
   return n_traces <= 384 ? 16 : (n_traces <= 768 ? 8 : kStreamWaves);
 }
+
+// The segmented path: about kSegGrid workgroups in all, at most kSegMax
+// segments a trace (every workgroup adds up the net changes of the segments
+// before its own), each a whole number of evaluation chunks; workgroups of 16
+// waves while they are at most kSegWide.
+// It costs 2 bytes a row and 16 bytes a cell more than one workgroup per
+// trace, and wins where those leave the chip idle: up to kSegTraces traces
+// (kSegStage for the stage shares, which have no workgroups above 4 waves).
+// Up to kSegSparse it still wins where a workgroup's step is bound by its
+// chunk of windows, not by its tile of rows (measured, one workgroup per trace
+// against segments: 500 traces x 32 models x 250 ms windows, 0.3 tiles a
+// chunk, 2876 / 1733 us; 768 of them, 0.6 tiles, 3275 / 2599; 401 x 13 models
+// x 200 ms, 1.4 tiles, 1698 / 1430; 300 x 16 models x 500 ms, 2.1 tiles, 1062 /
+// 1144; 768 x 8 models x 500 ms, 4.2 tiles, 580 / 1019; 200 x 8 models x 500 ms,
+// 2.1 tiles, 387 / 460; 128 x 8 models x 1 s, 4.2 tiles, 1345 / 1165).
+constexpr size_t kSegScratchMax = 1ull << 30;
+constexpr int64_t kSegTraces = 160, kSegStage = 384, kSegSparse = 768, kSegGrid = 2048, kSegMax = 256, kSegWide = 512;
 
 static size_t stream_lds(const tre_events* ev, bool stage = false) {
   const size_t M = (size_t)ev->cfg.n_models, C = (size_t)chunk_windows(ev->cfg.n_models, ev->wcap);
@@ -1881,12 +2850,15 @@ extern "C" int tre_load_events(const int64_t* ts, const uint8_t* model, const ui
     rc = validate_events(ev, st);
     if (rc != TRE_OK) return cleanup(rc);
   }
+  count_handle(ev->device, 1);
+  ev->counted = true;
   *out = ev;
   return TRE_OK;
 }
 
 extern "C" void tre_free_events(tre_events* ev) {
   if (!ev) return;
+  if (ev->counted) count_handle(ev->device, -1);
   if (ev->d_off) (void)hipFree(ev->d_off);
   if (ev->d_tick_window) (void)hipFree(ev->d_tick_window);
   if (ev->d_tick_kind) (void)hipFree(ev->d_tick_kind);
@@ -1975,8 +2947,9 @@ static StreamParams stream_params(const tre_events* ev, const tre_profile* prof)
   p.M = ev->cfg.n_models;
   p.wcap = ev->wcap;
   p.chunk = chunk_windows(ev->cfg.n_models, ev->wcap);
-  p.fast_w = (int32_t)(ev->cfg.fast_period_ms / ev->cfg.window_ms);
-  p.slow_w = (int32_t)(ev->cfg.slow_period_ms / ev->cfg.window_ms);
+  // a period longer than the trace never ticks
+  p.fast_w = (int32_t)std::min<int64_t>(ev->cfg.fast_period_ms / ev->cfg.window_ms, ev->n_windows + 1);
+  p.slow_w = (int32_t)std::min<int64_t>(ev->cfg.slow_period_ms / ev->cfg.window_ms, ev->n_windows + 1);
   p.magic_fast = p.fast_w == 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / (uint64_t)p.fast_w);
   p.magic_slow = p.slow_w == 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / (uint64_t)p.slow_w);
   p.n_ticks = (int32_t)ev->n_ticks;
@@ -1999,8 +2972,149 @@ __global__ __launch_bounds__(256) void sweep_map(const tre_scenario* sc, uint32_
   if (atomicAdd(&count[t], 1u) == 0u) first[t] = s;
 }
 
-static int launch_stream(const tre_events* ev, const StreamParams& p, hipStream_t st) {
+namespace {
+// the segmented path's shape and scratch for one call
+struct SegPlan {
+  int32_t nseg = 0, seg_w = 0, K = 0, chunk_log2 = 0, waves = 0;
+  size_t raw = 0, net = 0, row = 0, first = 0, bytes = 0;  // offsets of the scratch arrays, total
+};
+
+SegPlan seg_plan(const tre_events* ev, bool stage) {
+  SegPlan g;
+  const int64_t T = ev->n_traces, M = ev->cfg.n_models, nW = ev->n_windows;
+  const int64_t C = chunk_windows((int)M, ev->wcap);
+  if (T > (stage ? kSegStage : kSegTraces)) {
+    const double chunk_rows = (double)C * (double)ev->n_events / ((double)T * (double)nW);
+    const int64_t tile = (int64_t)(stage ? kStreamWaves : stream_waves((uint32_t)T)) * 64 * kStreamEPT;
+    if (T > kSegSparse || chunk_rows > 1.5 * (double)tile) return g;
+  }
+  const int64_t most = std::min<int64_t>({(int64_t)kSegMax, (kSegGrid + T - 1) / T, (nW + C - 1) / C});
+  if (most < 2) return g;
+  const int64_t per = (nW + most - 1) / most;
+  g.seg_w = (int32_t)((per + C - 1) / C * C);
+  const int64_t nseg = (nW + g.seg_w - 1) / g.seg_w;
+  if (nseg < 2) return g;
+  g.K = (int32_t)(stage ? 2 * M : M);
+  while ((2 << g.chunk_log2) <= kChainWindows && (g.K << (g.chunk_log2 + 1)) <= kChainCells) ++g.chunk_log2;
+  g.waves = T * nseg <= kSegWide ? 16 : kStreamWaves;
+  auto take = [&](size_t n) {
+    const size_t at = g.bytes;
+    g.bytes += (n + 255) & ~(size_t)255;
+    return at;
+  };
+  g.raw = take((size_t)T * g.K * nW * sizeof(double));
+  g.net = take((size_t)T * nseg * M * sizeof(unsigned long long));
+  g.row = take((size_t)T * (nseg + 1) * sizeof(int32_t));
+  g.first = take((size_t)T * g.K * sizeof(uint32_t));
+  if (g.bytes > kSegScratchMax) return g;
+  g.nseg = (int32_t)nseg;  // > 0: the path applies
+  return g;
+}
+}  // namespace
+
+static int launch_segments(const tre_events* ev, const SegPlan& g, StreamParams p, bool stage, char* ws,
+                           hipStream_t st) {
+  LaunchTimer lt("tss_stream", st);
+  const int M = ev->cfg.n_models;
+  const unsigned T = ev->n_traces, blocks = T * (unsigned)g.nseg;
+  SegNetParams np{};
+  np.ts = p.ts;
+  np.model = p.model;
+  np.type = p.type;
+  np.off = p.off;
+  np.window_ms = p.window_ms;
+  np.n_windows = p.n_windows;
+  np.M = M;
+  np.nseg = g.nseg;
+  np.seg_w = g.seg_w;
+  np.seg_row = (int32_t*)(ws + g.row);
+  np.seg_net = (unsigned long long*)(ws + g.net);
+  np.first = (uint32_t*)(ws + g.first);
+  np.K = g.K;
+  hipLaunchKernelGGL(seg_net, dim3(blocks), dim3(kNetThreads), 0, st, np);
+  p.nseg = g.nseg;
+  p.seg_w = g.seg_w;
+  p.seg_row = np.seg_row;
+  p.seg_net = np.seg_net;
+  p.raw = (double*)(ws + g.raw);
+  p.first = np.first;
+  const size_t ring = ev->wcap * (4 * (size_t)M + 1) * 8;
+  if (stage && g.waves == 16)
+    hipLaunchKernelGGL((tss_seg<16, kStreamEPT, true>), dim3(blocks), dim3(16 * 64), ring, st, p);
+  else if (stage)
+    hipLaunchKernelGGL((tss_seg<kStreamWaves, kStreamEPT, true>), dim3(blocks), dim3(kStreamWaves * 64), ring, st, p);
+  else if (g.waves == 16)
+    hipLaunchKernelGGL((tss_seg<16, kStreamEPT, false>), dim3(blocks), dim3(16 * 64), ring, st, p);
+  else
+    hipLaunchKernelGGL((tss_seg<kStreamWaves, kStreamEPT, false>), dim3(blocks), dim3(kStreamWaves * 64), ring, st, p);
+  ChainParams c{};
+  c.raw = p.raw;
+  c.first = p.first;
+  c.prof = p.prof;
+  c.n_windows = p.n_windows;
+  c.M = M;
+  c.chunk_log2 = g.chunk_log2;
+  c.fast_w = p.fast_w;
+  c.slow_w = p.slow_w;
+  c.n_ticks = p.n_ticks;
+  {
+    int64_t a = p.fast_w, b = p.slow_w;
+    while (b) {
+      const int64_t r = a % b;
+      a = b;
+      b = r;
+    }
+    c.both_w = (int32_t)std::min<int64_t>((int64_t)p.fast_w / a * p.slow_w, INT_MAX);
+    c.magic_fast = p.magic_fast;
+    c.magic_slow = p.magic_slow;
+    c.magic_both = c.both_w == 1 ? 0xFFFFFFFFu : (uint32_t)((1ull << 32) / (uint64_t)c.both_w);
+  }
+  c.magic_k = (1u << 20) / (uint32_t)g.K + 1u;
+  c.tss64 = stage ? p.stage64 : p.tss64;
+  c.tss32 = stage ? p.stage32 : p.tss32;
+  c.flags = stage ? p.sflags : p.flags;
+  c.snap = p.snap;
+  c.tick_window = ev->d_tick_window;
+  c.tick_kind = ev->d_tick_kind;
+  c.sc = p.sc;
+  c.sc_count = p.sc_count;
+  c.sc_first = p.sc_first;
+  c.ctl_one = p.ctl_one;
+  c.budget = p.budget;
+  c.moves = p.moves;
+  c.move_cap = p.move_cap;
+  c.n_moves = p.n_moves;
+  c.r_final = p.r_final;
+  c.r_windows = p.r_windows;
+  c.stride = 9;
+  while (c.stride < g.K) c.stride = 2 * c.stride - 1;
+  if (g.K > kChainRows && c.stride < 33) c.stride = 33;
+  const size_t lds = (6 * sizeof(double) * (size_t)c.stride) << g.chunk_log2;
+  const bool rows = g.K <= kChainRows;
+  const dim3 block(chain_threads(rows));
+  if (stage && rows) hipLaunchKernelGGL((chain_smooth<true, true>), dim3(T), block, lds, st, c);
+  else if (stage) hipLaunchKernelGGL((chain_smooth<true, false>), dim3(T), block, lds, st, c);
+  else if (!(c.tss64 || c.tss32 || c.flags || c.snap)) {}  // tallies only
+  else if (rows) hipLaunchKernelGGL((chain_smooth<false, true>), dim3(T), block, lds, st, c);
+  else hipLaunchKernelGGL((chain_smooth<false, false>), dim3(T), block, lds, st, c);
+  const hipError_t e = hipGetLastError();
+  lt.done();
+  if (e != hipSuccess) return fail(TRE_EHIP, "tss_stream launch: %s", hipGetErrorString(e));
+  return TRE_OK;
+}
+
+// ws, ws_bytes: scratch the caller holds for the segmented path; without it
+// the call takes its own from the pool
+static int launch_stream(const tre_events* ev, const StreamParams& p, hipStream_t st, char* ws = nullptr,
+                         size_t ws_bytes = 0) {
   const bool stage = p.stage64 || p.stage32 || p.sflags;
+  const SegPlan g = seg_plan(ev, stage);
+  if (g.nseg && ws) {
+    if (g.bytes <= ws_bytes) return launch_segments(ev, g, p, stage, ws, st);
+  } else if (g.nseg) {
+    const Scratch sx(ev->device, g.bytes, st);
+    if (sx.get()) return launch_segments(ev, g, p, stage, sx.get(), st);
+  }
   const size_t lds = stream_lds(ev, stage);
   LaunchTimer lt("tss_stream", st);
   const bool cells = p.prefill || p.decode || p.a_int || p.w_int || p.tss64 || p.tss32 || p.flags;
@@ -2051,6 +3165,11 @@ static int act_windows(const tre_events* ev, const tre_actuation* act, ActWindow
   return TRE_OK;
 }
 
+// a workgroup of four waves per scenario while the chip holds them all at
+// once (1024 scenarios x 720 ticks x 8 models: 223 us against 526 us with one
+// wave each); above, the folds' fewer instructions count
+constexpr uint32_t kOrdScenarios = 2048;
+
 static int launch_rebalance(const tre_events* ev, const tre_profile* prof, const double* vals,
                             const uint8_t* flags, const tre_scenario* sc, uint32_t n_sc,
                             const tre_ctl_out* out, const ActWindows* aw, hipStream_t st,
@@ -2083,7 +3202,11 @@ static int launch_rebalance(const tre_events* ev, const tre_profile* prof, const
   // one wave per scenario, four per workgroup
   const dim3 grid((unsigned)(((uint64_t)n_sc + 3) / 4)), block(256);
   LaunchTimer lt("rebalance", st);
-  if (aw)
+  if (n_sc <= kOrdScenarios && aw)
+    hipLaunchKernelGGL(rebalance_ordered<true>, dim3(n_sc), dim3(64 * (kOrdWaves + 1)), 0, st, c);
+  else if (n_sc <= kOrdScenarios)
+    hipLaunchKernelGGL(rebalance_ordered<false>, dim3(n_sc), dim3(64 * (kOrdWaves + 1)), 0, st, c);
+  else if (aw)
     hipLaunchKernelGGL(rebalance<true>, grid, block, 0, st, c);
   else
     hipLaunchKernelGGL(rebalance<false>, grid, block, 0, st, c);
@@ -2150,7 +3273,8 @@ static int rebalance_impl(const tre_events* ev, const tre_profile* prof, const d
 
 static int sweep_impl(const tre_events* ev, const tre_profile* prof, const tre_scenario* sc,
                       uint32_t n_scenarios, const tre_actuation* act, const tre_ctl_out* out,
-                      float* tss32, void* ws, size_t ws_bytes, void* stream, const char* who) {
+                      float* tss32, void* ws, size_t ws_bytes, void* stream, const char* who,
+                      bool own_scratch = false) {
   if (!ev || !prof) return fail(TRE_EINVAL, "%s: NULL argument", who);
   if (n_scenarios && !sc) return fail(TRE_EINVAL, "%s: NULL scenarios", who);
   int rc = check_ctl_out(out, n_scenarios);
@@ -2172,16 +3296,7 @@ static int sweep_impl(const tre_events* ev, const tre_profile* prof, const tre_s
   // it in the stream (rebalance skips it)
   uint32_t* count = nullptr;
   if (n_scenarios && !act) {
-    count = (uint32_t*)((char*)ws + snapshot_bytes(ev));
-    uint32_t* first = count + ev->n_traces;
-    hipLaunchKernelGGL(zero_u32, dim3((ev->n_traces + 255) / 256), dim3(256), 0, st, count, ev->n_traces);
-    hipLaunchKernelGGL(sweep_map, dim3((n_scenarios + 255) / 256), dim3(256), 0, st, sc, n_scenarios,
-                       ev->n_traces, count, (uint32_t*)first);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(TRE_EHIP, "sweep_map launch: %s", hipGetErrorString(e));
     p.sc = sc;
-    p.sc_count = count;
-    p.sc_first = first;
     p.budget = ev->cfg.budget;
     p.moves = out->moves;
     p.move_cap = out->move_cap;
@@ -2189,8 +3304,27 @@ static int sweep_impl(const tre_events* ev, const tre_profile* prof, const tre_s
     p.r_final = out->r_final;
     p.r_windows = out->r_windows;
   }
-  rc = launch_stream(ev, p, st);
-  if (rc || n_scenarios == 0) return rc;
+  // (with one trace the host knows: no map)
+  if (n_scenarios == 1 && !act && ev->n_traces == 1) {
+    p.ctl_one = 1;
+  } else if (n_scenarios && !act && ev->n_traces > 1) {
+    count = (uint32_t*)((char*)ws + snapshot_bytes(ev));
+    uint32_t* first = count + ev->n_traces;
+    hipLaunchKernelGGL(zero_u32, dim3((ev->n_traces + 255) / 256), dim3(256), 0, st, count, ev->n_traces);
+    hipLaunchKernelGGL(sweep_map, dim3((n_scenarios + 255) / 256), dim3(256), 0, st, sc, n_scenarios,
+                       ev->n_traces, count, (uint32_t*)first);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(TRE_EHIP, "sweep_map launch: %s", hipGetErrorString(e));
+    p.sc_count = count;
+    p.sc_first = first;
+  }
+  // own_scratch: what lies past the sweep's own part of ws serves the segments
+  const size_t used = (need + 255) & ~(size_t)255;
+  if (own_scratch)
+    rc = launch_stream(ev, p, st, (char*)ws + used, ws_bytes > used ? ws_bytes - used : 0);
+  else
+    rc = launch_stream(ev, p, st);
+  if (rc || n_scenarios == 0 || p.ctl_one) return rc;
   return launch_rebalance(ev, prof, (const double*)ws, nullptr, sc, n_scenarios, out,
                           act ? &aw : nullptr, st, count);
 }
@@ -2248,7 +3382,7 @@ extern "C" int tre_sweep_noalloc(const tre_events* ev, const tre_profile* prof, 
   if ((rc = scratch_for(ev->device, &ws))) return rc;
   tre_internal::NoTimingScope quiet;  // no event objects are created for this call
   return sweep_impl(ev, prof, sc, n_scenarios, nullptr, out, tss32, ws, (size_t)TRE_NOALLOC_SCRATCH_BYTES, stream,
-                    "tre_sweep_noalloc");
+                    "tre_sweep_noalloc", true);
 }
 
 extern "C" int tre_rebalance_act(const tre_events* ev, const tre_profile* prof, const double* tss64,

@@ -28,6 +28,7 @@ struct tre_events {
   std::vector<int64_t> h_off;
   uint32_t wcap;
   int device;
+  bool counted = false;  // among the device's live handles
 };
 
 namespace tre_internal {
