@@ -2103,8 +2103,10 @@ enum { kValOrder = 0, kValSchema = 1, kValRange = 2, kValState = 3, kValKinds = 
 struct ValParams {
   const int64_t* ts;
   const uint8_t* model;
+  const uint32_t* req;  // or NULL
   const uint8_t* type;
   const int64_t* off;
+  const uint64_t* sub_off;   // [n_traces + 1] pieces of the traces before each
   uint32_t n_traces;
   int64_t duration_ms;
   int64_t window_ms;
@@ -2112,29 +2114,132 @@ struct ValParams {
   int64_t max_per_window;
   unsigned* err;             // bit k: an error of kind k
   unsigned long long* first; // [kValKinds] lowest failing row of each kind
+  unsigned long long* net;   // per trace [M][pieces]: net changes of the counts in each piece
+  uint2* sub_max;            // [all pieces] largest id of an admission, of an ARRIVE or FINISH row
 };
 
-constexpr int kValChunk = 16384;
+// A trace's rows in pieces of kSubRows, one wave each: few traces then still
+// fill the chip (4 traces of 1.9 M rows are 3760 waves).
+constexpr int kSubRows = 2048;
+constexpr int kValChunk = 4 * kSubRows;  // rows of one workgroup of the load-time checks
 
+// One pass over the rows: order, schema and per-window range of each row, the
+// net change of each model's active and waiting counts over each piece (for
+// validate_state), and the largest ids (they size the id tables). Bound by
+// the 14 bytes a row; the windows of a row and of the one max_per_window
+// later are divided out only when less than a window apart (two 64-bit
+// divisions a row cost 30 of 85 us on 7.7 M rows).
 __global__ __launch_bounds__(256) void validate(ValParams p) {
+  __shared__ unsigned long long s_net[4][TRE_MAX_MODELS];
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
   for (uint32_t t = blockIdx.y; t < p.n_traces; t += gridDim.y) {
     const int64_t b = p.off[t], e = p.off[t + 1];
-    const int64_t c0 = b + (int64_t)blockIdx.x * kValChunk;
-    if (c0 >= e) continue;
-    const int64_t c1 = c0 + kValChunk < e ? c0 + kValChunk : e;
-    for (int64_t i = c0 + threadIdx.x; i < c1; i += 256) {
-      const int64_t t_i = p.ts[i];
-      const uint32_t ty = p.type[i];
-      unsigned bad = 0;
-      if (t_i < 0 || t_i >= p.duration_ms || (i > b && t_i < p.ts[i - 1])) bad |= 1u << kValOrder;
-      if (p.model[i] >= p.M || (ty & 0x7Cu) || ((ty & TRE_ADMIT) && (ty & 3u) != TRE_PREFILL))
-        bad |= 1u << kValSchema;
-      const int64_t j = i + p.max_per_window;
-      if (!(bad & 1u) && j < e && p.ts[j] / p.window_ms == t_i / p.window_ms) bad |= 1u << kValRange;
-      if (bad) {
-        atomicOr(p.err, bad);
-        for (int k = 0; k < kValState; ++k)
-          if (bad & (1u << k)) atomicMin(&p.first[k], (unsigned long long)i);
+    const int64_t c0 = b + (int64_t)blockIdx.x * kValChunk + (int64_t)wv * kSubRows;
+    if (c0 >= e) continue;  // whole wave; the waves share no barrier
+    const int64_t c1 = c0 + kSubRows < e ? c0 + kSubRows : e;
+    unsigned long long* const net = s_net[wv];
+    net[lane] = 0ull;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    uint32_t mxa = 0, mxl = 0;
+    constexpr int kU = 4;  // rows a lane loads before it uses any
+    for (int64_t i0 = c0 + lane; i0 < c1; i0 += 64 * kU) {
+      int64_t tv[kU], tp[kU], tj[kU];
+      uint32_t ty[kU], md[kU], id[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t i = i0 + 64 * u < c1 ? i0 + 64 * u : c1 - 1;  // past the piece, its last row again
+        tv[u] = p.ts[i];
+        tp[u] = p.ts[i > b ? i - 1 : b];
+        tj[u] = p.ts[i + p.max_per_window < e ? i + p.max_per_window : e - 1];
+        ty[u] = p.type[i];
+        md[u] = p.model[i];
+        id[u] = p.req ? p.req[i] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t i = i0 + 64 * u;
+        if (i >= c1) break;
+        const int64_t t_i = tv[u];
+        unsigned bad = 0;
+        if (t_i < 0 || t_i >= p.duration_ms || t_i < tp[u]) bad |= 1u << kValOrder;
+        if (md[u] >= (uint32_t)p.M || (ty[u] & 0x7Cu) || ((ty[u] & TRE_ADMIT) && (ty[u] & 3u) != TRE_PREFILL))
+          bad |= 1u << kValSchema;
+        if (!(bad & (1u << kValOrder)) && i + p.max_per_window < e && tj[u] < t_i + p.window_ms &&
+            tj[u] / p.window_ms == t_i / p.window_ms)
+          bad |= 1u << kValRange;
+        if (bad) {
+          atomicOr(p.err, bad);
+          for (int k = 0; k < kValState; ++k)
+            if (bad & (1u << k)) atomicMin(&p.first[k], (unsigned long long)i);
+        }
+        const uint32_t kind = ty[u] & 3u;
+        const bool admit = ty[u] == (TRE_PREFILL | TRE_ADMIT);
+        if (admit) mxa = id[u] > mxa ? id[u] : mxa;
+        if (kind == TRE_ARRIVE || kind == TRE_FINISH) mxl = id[u] > mxl ? id[u] : mxl;
+        // counts as validate_state reads them: waiting in the low word, active in the high one
+        const bool arrive = ty[u] == TRE_ARRIVE, finish = ty[u] == TRE_FINISH;
+        if (arrive || admit || finish)
+          atomicAdd(&net[md[u] & 63u],
+                    arrive ? 1ull : admit ? (1ull << 32) - 1ull : 0xFFFFFFFF00000000ull);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint64_t so = p.sub_off[t], n_sub = p.sub_off[t + 1] - so;
+    if (lane < p.M) p.net[so * p.M + (uint64_t)lane * n_sub + (uint64_t)((c0 - b) / kSubRows)] = net[lane];
+    if (p.req) {
+      for (int d = 32; d >= 1; d >>= 1) {
+        const uint32_t oa = (uint32_t)__shfl_xor((int)mxa, d), ol = (uint32_t)__shfl_xor((int)mxl, d);
+        mxa = oa > mxa ? oa : mxa;
+        mxl = ol > mxl ? ol : mxl;
+      }
+      if (lane == 0) p.sub_max[so + (uint64_t)((c0 - b) / kSubRows)] = make_uint2(mxa, mxl);
+    }
+  }
+}
+
+// the pieces' net changes of each (trace, model) into the counts before each
+// piece, in place: one wave per model at a time, 64 pieces a step; one more
+// wave's turn takes the largest ids of the trace (an atomicMax of every piece
+// on the trace's words held `validate` back: 7.7 M rows 154 us against 27)
+__global__ __launch_bounds__(256) void net_scan(unsigned long long* net, const uint64_t* sub_off, uint32_t n_traces,
+                                                int M, const uint2* sub_max, uint32_t* max_admit, uint32_t* max_life) {
+  const int wv = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
+  for (uint32_t t = blockIdx.x; t < n_traces; t += gridDim.x) {
+    const uint64_t so = sub_off[t], n = sub_off[t + 1] - so;
+    for (int m = (int)blockIdx.y * 4 + wv; m < M + (sub_max ? 1 : 0); m += 4 * (int)gridDim.y) {
+      if (m == M) {
+        uint32_t a = 0, l = 0;
+        for (uint64_t k = lane; k < n; k += 64) {
+          const uint2 v = sub_max[so + k];
+          a = v.x > a ? v.x : a;
+          l = v.y > l ? v.y : l;
+        }
+        for (int d = 32; d >= 1; d >>= 1) {
+          const uint32_t oa = (uint32_t)__shfl_xor((int)a, d), ol = (uint32_t)__shfl_xor((int)l, d);
+          a = oa > a ? oa : a;
+          l = ol > l ? ol : l;
+        }
+        if (lane == 0) {
+          max_admit[t] = a;
+          max_life[t] = l;
+        }
+        break;
+      }
+      unsigned long long* const x = net + so * M + (uint64_t)m * n;
+      unsigned long long carry = 0ull;
+      for (uint64_t k0 = 0; k0 < n; k0 += 64) {
+        const bool in = k0 + lane < n;
+        const unsigned long long v = in ? x[k0 + lane] : 0ull;
+        unsigned long long incl = v;
+        for (int o = 1; o < 64; o <<= 1) {
+          const unsigned long long u = __shfl_up(incl, o);
+          if (lane >= o) incl += u;
+        }
+        if (in) x[k0 + lane] = carry + incl - v;
+        carry += __shfl(incl, 63);
       }
     }
   }
@@ -2147,20 +2252,26 @@ __global__ __launch_bounds__(256) void validate(ValParams p) {
 // instant are checked (rows of one instant may come in any order). For
 // model m that is the count after its last row with that timestamp.
 //
-// One wave per trace (the trace's rows are already known sorted, with valid
-// models and types), 64 rows per step, one per lane. Rows of the same model
-// are found with ballots over the model's bits; a lane's count is its
-// model's carry plus the signed transitions of the same-model lanes up to
-// it. A row whose next same-model row in the step has a later timestamp is
-// the last of its instant and is checked at once; the model's last row of a
-// step is checked when the model's next row (in a later step) has a later
-// timestamp, or at the end of the trace. Per-model state (carries, the
-// timestamp and row of the last row seen) lives in the wave's LDS slice.
+// One wave per piece of a trace, 64 rows per step, one per lane, from the
+// counts before the piece (net_scan); on rows that fail the other checks the
+// result is not read. Rows of the same model are found with ballots over the
+// model's bits; a lane's count is its model's carry plus the signed
+// transitions of the same-model lanes up to it. A row whose next same-model
+// row in the step has a later timestamp is the last of its instant and is
+// checked at once; the model's last row of a step is checked when the
+// model's next row (in a later step) has a later timestamp, or at the end of
+// the piece, unless the rows after the piece go on with the model at the same
+// instant. Per-model state (carries, the timestamp and row of the last row
+// seen) lives in the wave's LDS slice. A step is a chain of ballots and LDS
+// round trips (about 0.8 us alone), so it is the waves in flight that count:
+// one wave per trace took 24.0 ms on 4 traces of 1.9 M rows.
 struct StateParams {
   const int64_t* ts;
   const uint8_t* model;
   const uint8_t* type;
   const int64_t* off;
+  const uint64_t* sub_off;
+  const unsigned long long* net;
   uint32_t n_traces;
   int32_t M;
   unsigned* err;
@@ -2169,193 +2280,195 @@ struct StateParams {
 
 __global__ __launch_bounds__(256) void validate_state(StateParams p) {
   __shared__ int s_a[4][TRE_MAX_MODELS], s_w[4][TRE_MAX_MODELS];  // counts after the rows seen
-  __shared__ long long s_t[4][TRE_MAX_MODELS];                     // timestamp of the model's last row, -1 none
-  __shared__ long long s_r[4][TRE_MAX_MODELS];                     // that row
-  const int wv = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-  const uint32_t t = blockIdx.x * 4u + (uint32_t)wv;
-  if (t >= p.n_traces) return;  // whole wave; the waves share no barrier
-  int* ca = s_a[wv];
-  int* cw = s_w[wv];
-  long long* lt = s_t[wv];
-  long long* lr = s_r[wv];
-  ca[lane] = 0;
-  cw[lane] = 0;
-  lt[lane] = -1;
-  lr[lane] = 0;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  __shared__ uint32_t s_t[4][TRE_MAX_MODELS];                      // timestamp of the model's last row
+  __shared__ int s_r[4][TRE_MAX_MODELS];                           // that row (from the trace's first), -1 none
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+  int* const ca = s_a[wv];
+  int* const cw = s_w[wv];
+  uint32_t* const lt = s_t[wv];
+  int* const lr = s_r[wv];
   const int nbits = p.M > 1 ? 32 - __clz(p.M - 1) : 0;
   const unsigned long long le = (2ull << lane) - 1ull;  // lanes <= this one
-  const int64_t b = p.off[t], e = p.off[t + 1];
-  long long bad = LLONG_MAX;
-  // rows of the next step are loaded before the current one is processed
-  auto load = [&](int64_t i, long long& ts, uint32_t& m, uint32_t& ty) {
-    const bool v = i < e;
-    ts = v ? (long long)p.ts[i] : 0;
-    m = v ? (uint32_t)p.model[i] & 63u : 0u;
-    ty = v ? (uint32_t)p.type[i] : 0xFFu;
+  auto fence = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  long long tsn;
-  uint32_t mn, tyn;
-  load(b + lane, tsn, mn, tyn);
-  for (int64_t r0 = b; r0 < e; r0 += 64) {
-    const int64_t i = r0 + lane;
-    const bool v = i < e;
-    const long long ts = tsn;
-    const uint32_t m = mn, ty = tyn;
-    load(i + 64, tsn, mn, tyn);
-    const int dA = (ty == (TRE_PREFILL | TRE_ADMIT) ? 1 : 0) - (ty == TRE_FINISH ? 1 : 0);
-    const int dW = (ty == TRE_ARRIVE ? 1 : 0) - (ty == (TRE_PREFILL | TRE_ADMIT) ? 1 : 0);
-    unsigned long long same = __ballot(v);
-    for (int k = 0; k < nbits; ++k) {
-      const unsigned long long bk = __ballot((m >> k) & 1u);
-      same &= ((m >> k) & 1u) ? bk : ~bk;
+  for (uint32_t t = blockIdx.y; t < p.n_traces; t += gridDim.y) {
+    const int64_t b = p.off[t];
+    const int n = (int)(p.off[t + 1] - b);  // below 2^27
+    const int sub = (int)blockIdx.x * 4 + wv;
+    if (sub * (int64_t)kSubRows >= n) continue;  // whole wave; the waves share no barrier
+    const int r_begin = sub * kSubRows, r_end = r_begin + kSubRows < n ? r_begin + kSubRows : n;
+    const uint64_t so = p.sub_off[t], n_sub = p.sub_off[t + 1] - so;
+    const unsigned long long before = lane < p.M ? p.net[so * p.M + (uint64_t)lane * n_sub + (uint64_t)sub] : 0ull;
+    ca[lane] = net_a(before);
+    cw[lane] = net_w(before);
+    lt[lane] = 0u;
+    lr[lane] = -1;
+    fence();
+    int bad = INT_MAX;
+    const int64_t* const ts_ = p.ts + b;
+    const uint8_t* const mo_ = p.model + b;
+    const uint8_t* const ty_ = p.type + b;
+    // rows of the next step are loaded before the current one is processed
+    auto load = [&](int i, uint32_t& ts, uint32_t& m, uint32_t& ty) {
+      const bool v = i < r_end;
+      const int k = v ? i : r_end - 1;
+      ts = (uint32_t)ts_[k];  // timestamps lie in [0, duration) below 2^32
+      m = (uint32_t)mo_[k] & 63u;
+      ty = v ? (uint32_t)ty_[k] : 0xFFu;
+    };
+    uint32_t tsn, mn, tyn;
+    load(r_begin + lane, tsn, mn, tyn);
+    for (int r0 = r_begin; r0 < r_end; r0 += 64) {
+      const int i = r0 + lane;
+      const bool v = i < r_end;
+      const uint32_t ts = tsn, m = mn, ty = tyn;
+      load(i + 64, tsn, mn, tyn);
+      const int dA = (ty == (TRE_PREFILL | TRE_ADMIT) ? 1 : 0) - (ty == TRE_FINISH ? 1 : 0);
+      const int dW = (ty == TRE_ARRIVE ? 1 : 0) - (ty == (TRE_PREFILL | TRE_ADMIT) ? 1 : 0);
+      unsigned long long same = __ballot(v);
+      for (int k = 0; k < nbits; ++k) {
+        const unsigned long long bk = __ballot((m >> k) & 1u);
+        same &= ((m >> k) & 1u) ? bk : ~bk;
+      }
+      const unsigned long long pa = __ballot(dA > 0), na = __ballot(dA < 0);
+      const unsigned long long pw = __ballot(dW > 0), nw = __ballot(dW < 0);
+      const unsigned long long upto = same & le;
+      const int ca0 = ca[m], cw0 = cw[m];
+      const int va = ca0 + __popcll(pa & upto) - __popcll(na & upto);
+      const int vw = cw0 + __popcll(pw & upto) - __popcll(nw & upto);
+      const unsigned long long after = same & ~le;
+      const int nl = after ? __ffsll((long long)after) - 1 : lane;
+      const uint32_t tnext = (uint32_t)__shfl((int)ts, nl);
+      // the last row of its instant inside this step
+      if (v && after && tnext != ts && (va < 0 || vw < 0)) bad = bad < i ? bad : i;
+      // the model's first row in this step settles its last row of an earlier step
+      if (v && (upto & ~(1ull << lane)) == 0ull && (ca0 < 0 || cw0 < 0)) {
+        const int rp = lr[m];
+        if (rp >= 0 && lt[m] != ts) bad = bad < rp ? bad : rp;
+      }
+      fence();
+      if (v && !after) {  // the model's last row in this step
+        ca[m] = va;
+        cw[m] = vw;
+        lt[m] = ts;
+        lr[m] = i;
+      }
+      fence();
     }
-    const unsigned long long pa = __ballot(dA > 0), na = __ballot(dA < 0);
-    const unsigned long long pw = __ballot(dW > 0), nw = __ballot(dW < 0);
-    const unsigned long long upto = same & le;
-    const int va = ca[m] + __popcll(pa & upto) - __popcll(na & upto);
-    const int vw = cw[m] + __popcll(pw & upto) - __popcll(nw & upto);
-    const unsigned long long after = same & ~le;
-    const int nl = after ? __ffsll((long long)after) - 1 : lane;
-    const long long tnext = __shfl(ts, nl);
-    // the last row of its instant inside this step
-    if (v && after && tnext != ts && (va < 0 || vw < 0)) bad = bad < i ? bad : i;
-    // the model's first row in this step settles its last row of an earlier step
-    if (v && (upto & ~(1ull << lane)) == 0ull) {
-      const long long tp = lt[m];
-      if (tp >= 0 && tp != ts && (ca[m] < 0 || cw[m] < 0)) bad = bad < lr[m] ? bad : lr[m];
+    // each model's last row is the last of its instant unless a later piece
+    // goes on with it: rows after this piece at the timestamp of its last row
+    const bool neg = lane < p.M && lr[lane] >= 0 && (ca[lane] < 0 || cw[lane] < 0);
+    bool on = false;
+    const uint32_t tl = (uint32_t)ts_[r_end - 1];
+    if (__ballot(neg && lt[lane] == tl)) {
+      for (int r0 = r_end; r0 < n; r0 += 64) {
+        const int i = r0 + lane < n ? r0 + lane : n - 1;
+        const bool at = r0 + lane < n && (uint32_t)ts_[i] == tl;
+        unsigned long long rows = __ballot(at);
+        const bool more = rows == ~0ull;
+        const int m = (int)mo_[i] & 63;
+        while (rows) {
+          const int l = __ffsll((long long)rows) - 1;
+          on = on || __builtin_amdgcn_readlane(m, l) == lane;
+          rows &= rows - 1ull;
+        }
+        if (!more) break;
+      }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (v && !after) {  // the model's last row in this step
-      ca[m] = va;
-      cw[m] = vw;
-      lt[m] = ts;
-      lr[m] = i;
+    if (neg && !(lt[lane] == tl && on)) bad = bad < lr[lane] ? bad : lr[lane];
+    if (bad != INT_MAX) {
+      atomicOr(p.err, 1u << kValState);
+      atomicMin(p.first, (unsigned long long)(b + bad));
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-  // each model's last row is the last of its instant
-  if (lane < p.M && lt[lane] >= 0 && (ca[lane] < 0 || cw[lane] < 0)) bad = bad < lr[lane] ? bad : lr[lane];
-  if (bad != LLONG_MAX) {
-    atomicOr(p.err, 1u << kValState);
-    atomicMin(p.first, (unsigned long long)bad);
+    fence();  // the next trace's state goes to the same slice
   }
 }
 
-// A request is admitted once (its first prefill chunk carries the ADMIT
-// bit). With request ids given, pass 1 finds the largest admitted id of
-// each trace; pass 2 sets one bit per admitted id in a per-trace bitmap
-// and records the smallest (trace, id) whose bit was already set.
-struct AdmitParams {
-  const uint32_t* req;
-  const uint8_t* type;
-  const int64_t* off;
-  uint32_t t0, n_traces;        // traces [t0, t0 + n_traces) of this launch
-  uint32_t* maxid;              // pass 1: [all traces] largest admitted id
-  const uint64_t* word_off;     // pass 2: [all traces] first bitmap word of each trace
-  uint64_t word_base;           // word_off of trace t0
-  uint32_t* bits;               // pass 2: bitmaps of this launch's traces
-  unsigned long long* dup;      // pass 2: smallest (trace << 32 | id) admitted twice
-};
-
-template <bool kMark>
-__global__ __launch_bounds__(256) void admit_scan(AdmitParams p) {
-  for (uint32_t tt = blockIdx.y; tt < p.n_traces; tt += gridDim.y) {
-    const uint32_t t = p.t0 + tt;
-    const int64_t b = p.off[t], e = p.off[t + 1];
-    const int64_t c0 = b + (int64_t)blockIdx.x * kValChunk;
-    if (c0 >= e) continue;  // uniform over the block
-    const int64_t c1 = c0 + kValChunk < e ? c0 + kValChunk : e;
-    uint32_t mx = 0;
-    for (int64_t i = c0 + threadIdx.x; i < c1; i += 256) {
-      if (p.type[i] != (TRE_PREFILL | TRE_ADMIT)) continue;
-      const uint32_t id = p.req[i];
-      if constexpr (!kMark) {
-        mx = id > mx ? id : mx;
-      } else {
-        if ((uint64_t)(id >> 5) >= p.word_off[t + 1] - p.word_off[t]) continue;  // above pass 1's largest id
-        const uint32_t bit = 1u << (id & 31u);
-        const uint32_t old = atomicOr(&p.bits[p.word_off[t] - p.word_base + (id >> 5)], bit);
-        if (old & bit) atomicMin(p.dup, ((unsigned long long)t << 32) | id);
-      }
-    }
-    if constexpr (!kMark) {
-      for (int d = 32; d >= 1; d >>= 1) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)mx, d);
-        mx = o > mx ? o : mx;
-      }
-      if ((threadIdx.x & 63) == 0 && mx) atomicMax(&p.maxid[t], mx);
-    }
-  }
-}
-
-// A request arrives once, finishes once, and neither arrives nor decodes
-// after it finished (rows of its FINISH instant in any order): the request
-// counts of Eq. (1) follow one lifecycle per id. Pass 0 finds the largest
-// id of an ARRIVE or FINISH row per trace; pass 1 marks each id's ARRIVE in
-// a bitmap and stores its FINISH timestamp (a second one of either is an
-// error); pass 2 checks every ARRIVE and DECODE row against the FINISH
-// timestamp of its id. The smallest (trace, id) in error is kept.
-struct LifeParams {
+// With request ids given, each id follows one lifecycle: a request is
+// admitted once (its first prefill chunk carries the ADMIT bit), arrives
+// once, finishes once, and neither arrives nor decodes after it finished
+// (rows of its FINISH instant in any order). The id_scan that marks sets one bit per
+// admitted and per arrived id in per-trace bitmaps and stores each id's
+// FINISH timestamp, and records the smallest (trace, id) whose mark was
+// already set; the id_scan that checks compares every ARRIVE and DECODE row with the FINISH
+// timestamp of its id. Bound by the atomics of the marks (three in eleven
+// rows). A bitmap of 2^k words holds id i in word i mod 2^k: ids count up
+// with time, and 32 neighbours in one word meet there (7.7 M rows 96 us
+// against 78).
+struct IdParams {
   const int64_t* ts;
   const uint32_t* req;
   const uint8_t* type;
   const int64_t* off;
   uint32_t t0, n_traces;        // traces [t0, t0 + n_traces) of this launch
-  uint32_t* maxid;              // pass 0: [all traces] largest id of an ARRIVE or FINISH row
-  const uint64_t* slot_off;     // passes 1, 2: [all traces] first slot of each trace's ids
-  uint64_t slot_base;           // slot_off of trace t0
+  const uint64_t* word_off;     // [all traces + 1] first bitmap word of each trace's admitted ids
+  const uint64_t* arr_off;      // [all traces + 1] the same of its arrived ids
+  const uint64_t* slot_off;     // [all traces + 1] first slot of each trace's ARRIVE and FINISH ids
+  uint64_t word_base, arr_base, slot_base;  // those of trace t0
+  uint32_t* bits;               // admitted ids of this launch's traces
+  uint32_t* arr;                // arrived ids
   uint32_t* fin;                // FINISH timestamp per slot, 0xFFFFFFFF when none
-  uint32_t* arr;                // ARRIVE bit per slot
-  unsigned long long* bad;      // smallest (trace << 32 | id) in error
+  unsigned long long* dup;      // smallest (trace << 32 | id) admitted twice
+  unsigned long long* bad;      // smallest (trace << 32 | id) off its lifecycle
 };
 
-template <int kPass>
-__global__ __launch_bounds__(256) void life_scan(LifeParams p) {
-  for (uint32_t tt = blockIdx.y; tt < p.n_traces; tt += gridDim.y) {
-    const uint32_t t = p.t0 + tt;
-    const int64_t b = p.off[t], e = p.off[t + 1];
-    const int64_t c0 = b + (int64_t)blockIdx.x * kValChunk;
-    if (c0 >= e) continue;  // uniform over the block
-    const int64_t c1 = c0 + kValChunk < e ? c0 + kValChunk : e;
-    uint32_t mx = 0;
-    for (int64_t i = c0 + threadIdx.x; i < c1; i += 256) {
-      const uint32_t ty = p.type[i], kind = ty & 3u, id = p.req[i];
-      if constexpr (kPass == 0) {
-        if ((kind == TRE_ARRIVE || kind == TRE_FINISH) && id > mx) mx = id;
-      } else {
-        if ((uint64_t)id >= p.slot_off[t + 1] - p.slot_off[t]) continue;  // no ARRIVE or FINISH of this id
-        const uint64_t sl = p.slot_off[t] - p.slot_base + id;
-        const uint32_t ts = (uint32_t)p.ts[i];  // timestamps lie in [0, duration) below 2^32
-        bool err = false;
-        if constexpr (kPass == 1) {
-          if (kind == TRE_ARRIVE) {
-            const uint32_t bit = 1u << (sl & 31u);
-            err = (atomicOr(&p.arr[sl >> 5], bit) & bit) != 0;
-          } else if (kind == TRE_FINISH) {
-            err = atomicCAS(&p.fin[sl], 0xFFFFFFFFu, ts) != 0xFFFFFFFFu;
-          }
-        } else {
-          if (kind == TRE_ARRIVE || kind == TRE_DECODE) {
-            const uint32_t f = p.fin[sl];
-            err = f != 0xFFFFFFFFu && ts > f;
-          }
+template <bool kCheck>
+__global__ __launch_bounds__(256) void id_scan(IdParams p) {
+  const uint32_t t = p.t0 + blockIdx.y;
+  const int64_t b = p.off[t], e = p.off[t + 1];
+  const int64_t c0 = b + (int64_t)blockIdx.x * kSubRows;
+  if (c0 >= e) return;
+  const int64_t c1 = c0 + kSubRows < e ? c0 + kSubRows : e;
+  const uint64_t n_words = p.word_off[t + 1] - p.word_off[t], w0 = p.word_off[t] - p.word_base;
+  const uint64_t n_arr = p.arr_off[t + 1] - p.arr_off[t], a0 = p.arr_off[t] - p.arr_base;
+  const uint64_t n_slots = p.slot_off[t + 1] - p.slot_off[t], s0 = p.slot_off[t] - p.slot_base;
+  const int kw = 63 - __clzll((long long)n_words), ka = 63 - __clzll((long long)n_arr);  // powers of two
+  constexpr int kU = 4;
+  for (int64_t i0 = c0 + threadIdx.x; i0 < c1; i0 += 256 * kU) {
+    uint32_t tyv[kU], idv[kU], tv[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int64_t i = i0 + 256 * u < c1 ? i0 + 256 * u : c1 - 1;
+      tyv[u] = i0 + 256 * u < c1 ? (uint32_t)p.type[i] : (uint32_t)TRE_PREFILL;  // a plain PREFILL row marks nothing
+      idv[u] = p.req[i];
+      tv[u] = (uint32_t)p.ts[i];  // timestamps lie in [0, duration) below 2^32
+    }
+    // every mark (or FINISH read) issued before any result is used
+    uint32_t old[kU], bit[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint32_t kind = tyv[u] & 3u, id = idv[u];
+      const bool slot = (uint64_t)id < n_slots;  // always, for ARRIVE and FINISH
+      const uint64_t sl = s0 + id;
+      if constexpr (!kCheck) {
+        const bool admit = tyv[u] == (TRE_PREFILL | TRE_ADMIT);
+        old[u] = 0u;
+        bit[u] = 0u;
+        const uint32_t b = id >> (admit ? kw : ka);
+        if ((admit || (kind == TRE_ARRIVE && slot)) && b < 32u) {  // always below, for ids up to the largest
+          uint32_t* const w = admit ? &p.bits[w0 + (id & (n_words - 1))] : &p.arr[a0 + (id & (n_arr - 1))];
+          bit[u] = 1u << b;
+          old[u] = atomicOr(w, bit[u]);
+        } else if (kind == TRE_FINISH && slot) {
+          old[u] = ~atomicCAS(&p.fin[sl], 0xFFFFFFFFu, tv[u]);
+          bit[u] = 0xFFFFFFFFu;  // set before when the word was not all ones
         }
-        if (err) atomicMin(p.bad, ((unsigned long long)t << 32) | id);
+      } else {
+        old[u] = 0xFFFFFFFFu;
+        if ((kind == TRE_ARRIVE || kind == TRE_DECODE) && slot) old[u] = p.fin[sl];
       }
     }
-    if constexpr (kPass == 0) {
-      for (int d = 32; d >= 1; d >>= 1) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)mx, d);
-        mx = o > mx ? o : mx;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const unsigned long long key = ((unsigned long long)t << 32) | idv[u];
+      if constexpr (!kCheck) {
+        if (old[u] & bit[u]) atomicMin((tyv[u] & 3u) == TRE_PREFILL ? p.dup : p.bad, key);
+      } else {
+        if (old[u] != 0xFFFFFFFFu && tv[u] > old[u]) atomicMin(p.bad, key);
       }
-      if ((threadIdx.x & 63) == 0 && mx) atomicMax(&p.maxid[t], mx);
     }
   }
 }
@@ -2570,203 +2683,181 @@ static size_t stream_lds(const tre_events* ev, bool stage = false) {
   return ring + 3 * C * M * 8 + M * sizeof(CtlModel) + ((11 * 4 + 7) & ~(size_t)7);
 }
 
+// Device memory of one call: from the pool, or its own when the pool gives none
+class CallMemory {
+ public:
+  CallMemory(int dev, size_t bytes, hipStream_t st) : pooled_(dev, bytes, st) {
+    if (!pooled_.get() && hipMalloc(&own_, bytes) != hipSuccess) {
+      own_ = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  ~CallMemory() {
+    if (own_) (void)hipFree(own_);
+  }
+  CallMemory(const CallMemory&) = delete;
+  CallMemory& operator=(const CallMemory&) = delete;
+  char* get() const { return own_ ? (char*)own_ : pooled_.get(); }
+
+ private:
+  Scratch pooled_;
+  void* own_ = nullptr;
+};
+
 // The load-time checks (synchronous): order, schema and per-window range
-// of every row; then, on valid rows, counts never negative; then, with
-// request ids, no id admitted twice. The error reported is the kind of the
+// of every row; on rows that pass, counts never negative; then, with
+// request ids, one lifecycle per id. The error reported is the kind of the
 // lowest failing row among the first three kinds (order before schema
 // before range on one row), else a negative count (its lowest row), else a
-// duplicate admission (the smallest trace, then id).
+// duplicate admission (the smallest trace, then id), else an id off its
+// lifecycle. Two waits in all: after the checks without ids, whose results
+// size the id tables, and at the end.
 static int validate_events(const tre_events* ev, hipStream_t st) {
   const uint32_t n_traces = ev->n_traces;
   const tre_trace_cfg& c = ev->cfg;
+  const size_t nt = n_traces;
   int64_t maxlen = 0;
-  for (uint32_t i = 0; i < n_traces; ++i) maxlen = std::max<int64_t>(maxlen, ev->h_off[i + 1] - ev->h_off[i]);
-  if (maxlen == 0) return TRE_OK;
-  // err (8 bytes), first rows [kValKinds], duplicate key
+  // one block, copied both ways at once: the results, the largest ids of each
+  // trace, the traces' first pieces
   struct Slots {
     unsigned err, pad;
     unsigned long long first[kValKinds];
     unsigned long long dup, life;
-  } h;
-  void* slots = nullptr;
-  if (hipMalloc(&slots, sizeof(Slots)) != hipSuccess) return fail(TRE_EHIP, "hipMalloc failed");
-  Slots* d = (Slots*)slots;
+  };
+  static_assert(sizeof(Slots) % 8 == 0, "");
+  const size_t max_at = sizeof(Slots), sub_at = max_at + 8 * nt, net_at = sub_at + 8 * (nt + 1);
+  std::vector<uint64_t> host(net_at / 8);
+  Slots& h = *(Slots*)host.data();
+  uint32_t* const h_admit = (uint32_t*)((char*)host.data() + max_at);
+  uint32_t* const h_life = h_admit + nt;
+  uint64_t* const h_sub = (uint64_t*)((char*)host.data() + sub_at);
   memset(&h, 0xFF, sizeof h);
   h.err = 0;
   h.pad = 0;
-  const dim3 grid((unsigned)((maxlen + kValChunk - 1) / kValChunk), std::min<uint32_t>(n_traces, 65535u));
-  auto readback = [&]() {
-    return hipMemcpyAsync(&h, d, sizeof h, hipMemcpyDeviceToHost, st) == hipSuccess &&
+  h_sub[0] = 0;
+  for (uint32_t i = 0; i < n_traces; ++i) {
+    const int64_t len = ev->h_off[i + 1] - ev->h_off[i];
+    maxlen = std::max(maxlen, len);
+    h_sub[i + 1] = h_sub[i] + (uint64_t)((len + kSubRows - 1) / kSubRows);
+  }
+  if (maxlen == 0) return TRE_OK;
+  const uint64_t net_bytes = h_sub[nt] * (uint64_t)c.n_models * 8;
+  CallMemory mem(ev->device, net_at + net_bytes + (ev->req ? h_sub[nt] * sizeof(uint2) : 0), st);
+  if (!mem.get()) return fail(TRE_EHIP, "hipMalloc failed");
+  Slots* const d = (Slots*)mem.get();
+  uint32_t* const d_admit = (uint32_t*)(mem.get() + max_at);
+  const uint64_t* const d_sub = (const uint64_t*)(mem.get() + sub_at);
+  unsigned long long* const d_net = (unsigned long long*)(mem.get() + net_at);
+  uint2* const d_smax = ev->req ? (uint2*)(mem.get() + net_at + net_bytes) : nullptr;
+  auto readback = [&](size_t bytes) {
+    return hipMemcpyAsync(host.data(), d, bytes, hipMemcpyDeviceToHost, st) == hipSuccess &&
            hipStreamSynchronize(st) == hipSuccess;
   };
-  bool ok = hipMemcpyAsync(d, &h, sizeof h, hipMemcpyHostToDevice, st) == hipSuccess;
+  bool ok = hipMemcpyAsync(d, host.data(), net_at, hipMemcpyHostToDevice, st) == hipSuccess;
+  const dim3 grid((unsigned)((maxlen + kValChunk - 1) / kValChunk), std::min<uint32_t>(n_traces, 65535u));
   if (ok) {
-    ValParams vp{ev->ts, ev->model, ev->type, ev->d_off, n_traces, c.duration_ms, c.window_ms, c.n_models,
-                 max_events_per_window(c.window_ms), &d->err, d->first};
+    ValParams vp{ev->ts, ev->model, ev->req, ev->type, ev->d_off, d_sub, n_traces, c.duration_ms, c.window_ms,
+                 c.n_models, max_events_per_window(c.window_ms), &d->err, d->first, d_net, d_smax};
     LaunchTimer lt("validate", st);
     hipLaunchKernelGGL(validate, grid, dim3(256), 0, st, vp);
     ok = hipGetLastError() == hipSuccess;
     lt.done();
   }
-  ok = ok && readback();
-  int rc = TRE_OK;
-  if (ok && h.err) {
+  if (ok) {
+    hipLaunchKernelGGL(net_scan, dim3(std::min<uint32_t>(n_traces, 65535u), (unsigned)(c.n_models / 4 + 1)), dim3(256), 0, st, d_net, d_sub, n_traces,
+                       c.n_models, d_smax, d_admit, d_admit + nt);
+    StateParams sp{ev->ts, ev->model, ev->type, ev->d_off, d_sub, d_net, n_traces, c.n_models, &d->err,
+                   &d->first[kValState]};
+    hipLaunchKernelGGL(validate_state, grid, dim3(256), 0, st, sp);
+    ok = hipGetLastError() == hipSuccess;
+  }
+  if (!ok || !readback(sub_at)) return fail(TRE_EHIP, "validation launch failed");
+  if (h.err) {
     int kind = -1;
     for (int k = 0; k < kValState; ++k)
       if ((h.err >> k & 1u) && (kind < 0 || h.first[k] < h.first[kind])) kind = k;
+    if (kind < 0)
+      return fail(TRE_ESTATE, "row %llu: an active or waiting count below zero after this instant",
+                  h.first[kValState]);
     const unsigned long long row = h.first[kind];
-    if (kind == kValOrder) rc = fail(TRE_EORDER, "row %llu: timestamp unsorted or outside [0, duration)", row);
-    else if (kind == kValSchema) rc = fail(TRE_ESCHEMA, "row %llu: model index or type byte invalid", row);
-    else
-      rc = fail(TRE_ERANGE, "row %llu: more than %lld events in one window", row,
+    if (kind == kValOrder) return fail(TRE_EORDER, "row %llu: timestamp unsorted or outside [0, duration)", row);
+    if (kind == kValSchema) return fail(TRE_ESCHEMA, "row %llu: model index or type byte invalid", row);
+    return fail(TRE_ERANGE, "row %llu: more than %lld events in one window", row,
                 (long long)max_events_per_window(c.window_ms));
   }
-  if (ok && rc == TRE_OK) {
-    StateParams sp{ev->ts, ev->model, ev->type, ev->d_off, n_traces, c.n_models, &d->err, &d->first[kValState]};
-    hipLaunchKernelGGL(validate_state, dim3((n_traces + 3) / 4), dim3(256), 0, st, sp);
-    ok = hipGetLastError() == hipSuccess && readback();
-    if (ok && (h.err >> kValState & 1u))
-      rc = fail(TRE_ESTATE, "row %llu: an active or waiting count below zero after this instant",
-                h.first[kValState]);
+  if (!ev->req) return TRE_OK;
+  // the id tables, in batches of traces of at most 2^26 bitmap words (256
+  // MiB) and 2^26 slots (256 MiB of FINISH timestamps), or one trace's if larger
+  std::vector<uint64_t> offs(3 * (nt + 1));
+  uint64_t* const woff = offs.data();
+  uint64_t* const aoff = woff + nt + 1;
+  uint64_t* const soff = aoff + nt + 1;
+  uint64_t most_w = 0, most_s = 0;
+  woff[0] = aoff[0] = soff[0] = 0;
+  auto words = [](uint32_t max_id) {  // a power of two whose bits hold ids 0 .. max_id
+    uint64_t w = 1;
+    while (32 * w <= max_id) w <<= 1;
+    return w;
+  };
+  for (uint32_t t = 0; t < n_traces; ++t) {
+    const uint64_t w = words(h_admit[t]), n = (uint64_t)h_life[t] + 1u;
+    woff[t + 1] = woff[t] + w;
+    aoff[t + 1] = aoff[t] + words(h_life[t]);
+    soff[t + 1] = soff[t] + n;
+    most_w = std::max(most_w, w);
+    most_s = std::max(most_s, n);
   }
-  if (ok && rc == TRE_OK && ev->req) {
-    // pass 1: largest admitted id per trace; then bitmaps of at most 2^26
-    // words (256 MiB) at a time, or one trace's if larger
-    uint32_t* d_max = nullptr;
-    uint64_t* d_woff = nullptr;
-    uint32_t* d_bits = nullptr;
-    std::vector<uint32_t> hmax(n_traces);
-    std::vector<uint64_t> woff(n_traces + 1);
-    ok = hipMalloc(&d_max, sizeof(uint32_t) * n_traces) == hipSuccess &&
-         hipMemsetAsync(d_max, 0, sizeof(uint32_t) * n_traces, st) == hipSuccess;
-    AdmitParams ap{};
-    ap.req = ev->req;
-    ap.type = ev->type;
-    ap.off = ev->d_off;
-    ap.maxid = d_max;
-    ap.dup = &d->dup;
-    for (uint32_t t0 = 0; ok && t0 < n_traces; t0 += 65535u) {
-      ap.t0 = t0;
-      ap.n_traces = std::min<uint32_t>(n_traces - t0, 65535u);
-      hipLaunchKernelGGL(admit_scan<false>, dim3(grid.x, ap.n_traces), dim3(256), 0, st, ap);
+  const uint64_t cap_w = std::max<uint64_t>(most_w, std::min<uint64_t>(woff[nt], 1ull << 26));
+  const uint64_t cap_s = std::max<uint64_t>(most_s, std::min<uint64_t>(soff[nt], 1ull << 26));
+  // a trace's words are at most 2 + a sixteenth of its slots
+  const uint64_t cap_a = cap_s / 16 + 2 * std::min<uint64_t>(nt, 65535u);
+  const size_t offs_bytes = offs.size() * 8;
+  CallMemory tab(ev->device, offs_bytes + 4 * (cap_a + cap_w + cap_s), st);
+  if (!tab.get()) return fail(TRE_EHIP, "hipMalloc failed");
+  ok = hipMemcpyAsync(tab.get(), woff, offs_bytes, hipMemcpyHostToDevice, st) == hipSuccess;
+  IdParams ip{};
+  ip.ts = ev->ts;
+  ip.req = ev->req;
+  ip.type = ev->type;
+  ip.off = ev->d_off;
+  ip.word_off = (const uint64_t*)tab.get();
+  ip.arr_off = ip.word_off + nt + 1;
+  ip.slot_off = ip.arr_off + nt + 1;
+  ip.arr = (uint32_t*)(tab.get() + offs_bytes);
+  ip.bits = ip.arr + cap_a;
+  ip.fin = ip.bits + cap_w;
+  ip.dup = &d->dup;
+  ip.bad = &d->life;
+  for (uint32_t t0 = 0; ok && t0 < n_traces;) {
+    uint32_t t1 = t0 + 1;
+    while (t1 < n_traces && t1 - t0 < 65535u && woff[t1 + 1] - woff[t0] <= cap_w && soff[t1 + 1] - soff[t0] <= cap_s)
+      ++t1;
+    int64_t len = 0;
+    for (uint32_t t = t0; t < t1; ++t) len = std::max<int64_t>(len, ev->h_off[t + 1] - ev->h_off[t]);
+    ip.t0 = t0;
+    ip.n_traces = t1 - t0;
+    ip.word_base = woff[t0];
+    ip.arr_base = aoff[t0];
+    ip.slot_base = soff[t0];
+    // the two bitmaps lie side by side
+    ok = hipMemsetAsync(ip.arr, 0, 4 * (cap_a + woff[t1] - woff[t0]), st) == hipSuccess &&
+         hipMemsetAsync(ip.fin, 0xFF, 4 * (soff[t1] - soff[t0]), st) == hipSuccess;
+    if (ok && len > 0) {
+      const dim3 g((unsigned)((len + kSubRows - 1) / kSubRows), t1 - t0);
+      hipLaunchKernelGGL(id_scan<false>, g, dim3(256), 0, st, ip);
+      hipLaunchKernelGGL(id_scan<true>, g, dim3(256), 0, st, ip);
       ok = hipGetLastError() == hipSuccess;
     }
-    ok = ok && hipMemcpyAsync(hmax.data(), d_max, sizeof(uint32_t) * n_traces, hipMemcpyDeviceToHost, st) ==
-                   hipSuccess &&
-         hipStreamSynchronize(st) == hipSuccess;
-    woff[0] = 0;
-    uint64_t most = 0;
-    for (uint32_t t = 0; t < n_traces; ++t) {
-      const uint64_t w = (uint64_t)(hmax[t] >> 5) + 1u;
-      woff[t + 1] = woff[t] + w;
-      most = std::max(most, w);
-    }
-    const uint64_t cap = std::max<uint64_t>(most, std::min<uint64_t>(woff[n_traces], 1ull << 26));
-    ok = ok && hipMalloc(&d_woff, sizeof(uint64_t) * (n_traces + 1)) == hipSuccess &&
-         hipMalloc(&d_bits, sizeof(uint32_t) * cap) == hipSuccess &&
-         hipMemcpyAsync(d_woff, woff.data(), sizeof(uint64_t) * (n_traces + 1), hipMemcpyHostToDevice, st) ==
-             hipSuccess;
-    ap.word_off = d_woff;
-    ap.bits = d_bits;
-    for (uint32_t t0 = 0; ok && t0 < n_traces;) {
-      uint32_t t1 = t0 + 1;
-      while (t1 < n_traces && t1 - t0 < 65535u && woff[t1 + 1] - woff[t0] <= cap) ++t1;
-      int64_t len = 0;
-      for (uint32_t t = t0; t < t1; ++t) len = std::max<int64_t>(len, ev->h_off[t + 1] - ev->h_off[t]);
-      ap.t0 = t0;
-      ap.n_traces = t1 - t0;
-      ap.word_base = woff[t0];
-      ok = hipMemsetAsync(d_bits, 0, sizeof(uint32_t) * (woff[t1] - woff[t0]), st) == hipSuccess;
-      if (ok && len > 0) {
-        hipLaunchKernelGGL(admit_scan<true>, dim3((unsigned)((len + kValChunk - 1) / kValChunk), t1 - t0),
-                           dim3(256), 0, st, ap);
-        ok = hipGetLastError() == hipSuccess;
-      }
-      t0 = t1;
-    }
-    ok = ok && readback();
-    if (d_max) (void)hipFree(d_max);
-    if (d_woff) (void)hipFree(d_woff);
-    if (d_bits) (void)hipFree(d_bits);
-    if (ok && h.dup != ~0ull)
-      rc = fail(TRE_ESTATE, "trace %u: request id %u admitted more than once", (unsigned)(h.dup >> 32),
+    t0 = t1;
+  }
+  if (!ok || !readback(sizeof(Slots))) return fail(TRE_EHIP, "validation launch failed");
+  if (h.dup != ~0ull)
+    return fail(TRE_ESTATE, "trace %u: request id %u admitted more than once", (unsigned)(h.dup >> 32),
                 (unsigned)h.dup);
-  }
-  if (ok && rc == TRE_OK && ev->req) {
-    // the lifecycle of each id: pass 0 sizes per-trace tables (ids up to the
-    // largest ARRIVE or FINISH id), passes 1 and 2 run over batches of at
-    // most 2^26 slots (256 MiB of FINISH timestamps), or one trace if larger
-    uint32_t* d_max = nullptr;
-    uint64_t* d_soff = nullptr;
-    uint32_t* d_fin = nullptr;
-    uint32_t* d_arr = nullptr;
-    std::vector<uint32_t> hmax(n_traces);
-    std::vector<uint64_t> soff(n_traces + 1);
-    ok = hipMalloc(&d_max, sizeof(uint32_t) * n_traces) == hipSuccess &&
-         hipMemsetAsync(d_max, 0, sizeof(uint32_t) * n_traces, st) == hipSuccess;
-    LifeParams lp{};
-    lp.ts = ev->ts;
-    lp.req = ev->req;
-    lp.type = ev->type;
-    lp.off = ev->d_off;
-    lp.maxid = d_max;
-    lp.bad = &d->life;
-    for (uint32_t t0 = 0; ok && t0 < n_traces; t0 += 65535u) {
-      lp.t0 = t0;
-      lp.n_traces = std::min<uint32_t>(n_traces - t0, 65535u);
-      hipLaunchKernelGGL(life_scan<0>, dim3(grid.x, lp.n_traces), dim3(256), 0, st, lp);
-      ok = hipGetLastError() == hipSuccess;
-    }
-    ok = ok && hipMemcpyAsync(hmax.data(), d_max, sizeof(uint32_t) * n_traces, hipMemcpyDeviceToHost, st) ==
-                   hipSuccess &&
-         hipStreamSynchronize(st) == hipSuccess;
-    soff[0] = 0;
-    uint64_t most = 0;
-    for (uint32_t t = 0; t < n_traces; ++t) {
-      const uint64_t n = (uint64_t)hmax[t] + 1u;
-      soff[t + 1] = soff[t] + n;
-      most = std::max(most, n);
-    }
-    const uint64_t cap = std::max<uint64_t>(most, std::min<uint64_t>(soff[n_traces], 1ull << 26));
-    ok = ok && hipMalloc(&d_soff, sizeof(uint64_t) * (n_traces + 1)) == hipSuccess &&
-         hipMalloc(&d_fin, sizeof(uint32_t) * cap) == hipSuccess &&
-         hipMalloc(&d_arr, sizeof(uint32_t) * (cap / 32 + 1)) == hipSuccess &&
-         hipMemcpyAsync(d_soff, soff.data(), sizeof(uint64_t) * (n_traces + 1), hipMemcpyHostToDevice, st) ==
-             hipSuccess;
-    lp.slot_off = d_soff;
-    lp.fin = d_fin;
-    lp.arr = d_arr;
-    for (uint32_t t0 = 0; ok && t0 < n_traces;) {
-      uint32_t t1 = t0 + 1;
-      while (t1 < n_traces && t1 - t0 < 65535u && soff[t1 + 1] - soff[t0] <= cap) ++t1;
-      int64_t len = 0;
-      for (uint32_t t = t0; t < t1; ++t) len = std::max<int64_t>(len, ev->h_off[t + 1] - ev->h_off[t]);
-      const uint64_t slots = soff[t1] - soff[t0];
-      lp.t0 = t0;
-      lp.n_traces = t1 - t0;
-      lp.slot_base = soff[t0];
-      ok = hipMemsetAsync(d_fin, 0xFF, sizeof(uint32_t) * slots, st) == hipSuccess &&
-           hipMemsetAsync(d_arr, 0, sizeof(uint32_t) * (slots / 32 + 1), st) == hipSuccess;
-      if (ok && len > 0) {
-        const dim3 g((unsigned)((len + kValChunk - 1) / kValChunk), t1 - t0);
-        hipLaunchKernelGGL(life_scan<1>, g, dim3(256), 0, st, lp);
-        hipLaunchKernelGGL(life_scan<2>, g, dim3(256), 0, st, lp);
-        ok = hipGetLastError() == hipSuccess;
-      }
-      t0 = t1;
-    }
-    ok = ok && readback();
-    if (d_max) (void)hipFree(d_max);
-    if (d_soff) (void)hipFree(d_soff);
-    if (d_fin) (void)hipFree(d_fin);
-    if (d_arr) (void)hipFree(d_arr);
-    if (ok && h.life != ~0ull)
-      rc = fail(TRE_ESTATE, "trace %u: request id %u arrives or finishes twice, or arrives or decodes after its FINISH",
+  if (h.life != ~0ull)
+    return fail(TRE_ESTATE, "trace %u: request id %u arrives or finishes twice, or arrives or decodes after its FINISH",
                 (unsigned)(h.life >> 32), (unsigned)h.life);
-  }
-  (void)hipFree(slots);
-  if (!ok) return fail(TRE_EHIP, "validation launch failed");
-  return rc;
+  return TRE_OK;
 }
 
 extern "C" int tre_load_events(const int64_t* ts, const uint8_t* model, const uint32_t* req,
@@ -2818,12 +2909,13 @@ extern "C" int tre_load_events(const int64_t* ts, const uint8_t* model, const ui
   const int64_t fw = c.fast_period_ms / c.window_ms, sw = c.slow_period_ms / c.window_ms;
   std::vector<uint32_t> tw;
   std::vector<uint8_t> tk;
-  for (int64_t w = 0; w < ev->n_windows; ++w) {
-    const uint8_t k = (uint8_t)(((w + 1) % fw == 0 ? 1 : 0) | ((w + 1) % sw == 0 ? 2 : 0));
-    if (k) {
-      tw.push_back((uint32_t)w);
-      tk.push_back(k);
-    }
+  // the windows that end on a multiple of either period, in order
+  for (int64_t f = fw, s = sw; f <= ev->n_windows || s <= ev->n_windows;) {
+    const int64_t x = std::min(f, s);
+    tw.push_back((uint32_t)(x - 1));
+    tk.push_back((uint8_t)((x == f ? 1 : 0) | (x == s ? 2 : 0)));
+    if (x == f) f += fw;
+    if (x == s) s += sw;
   }
   ev->n_ticks = (int64_t)tw.size();
   hipStream_t st = (hipStream_t)stream;
@@ -2833,16 +2925,17 @@ extern "C" int tre_load_events(const int64_t* ts, const uint8_t* model, const ui
     return code;
   };
   if (hipGetDevice(&ev->device) != hipSuccess) return cleanup(fail(TRE_EHIP, "hipGetDevice failed"));
-  if (hipMalloc(&ev->d_off, sizeof(int64_t) * (n_traces + 1)) != hipSuccess ||
-      hipMalloc(&ev->d_tick_window, sizeof(uint32_t) * (tw.size() + 1)) != hipSuccess ||
-      hipMalloc(&ev->d_tick_kind, tw.size() + 1) != hipSuccess)
+  // the handle's tables in one allocation and one copy: offsets, tick windows, tick kinds
+  const size_t off_bytes = sizeof(int64_t) * ((size_t)n_traces + 1), tw_bytes = sizeof(uint32_t) * (tw.size() + 1);
+  std::vector<char> tables(off_bytes + tw_bytes + tk.size() + 1);
+  memcpy(tables.data(), trace_off, off_bytes);
+  if (!tw.empty()) memcpy(tables.data() + off_bytes, tw.data(), sizeof(uint32_t) * tw.size());
+  if (!tk.empty()) memcpy(tables.data() + off_bytes + tw_bytes, tk.data(), tk.size());
+  if (hipMalloc(&ev->d_off, tables.size()) != hipSuccess)
     return cleanup(fail(TRE_EHIP, "hipMalloc of handle tables failed"));
-  if (hipMemcpyAsync(ev->d_off, trace_off, sizeof(int64_t) * (n_traces + 1), hipMemcpyHostToDevice,
-                     st) != hipSuccess ||
-      (!tw.empty() && hipMemcpyAsync(ev->d_tick_window, tw.data(), sizeof(uint32_t) * tw.size(),
-                                     hipMemcpyHostToDevice, st) != hipSuccess) ||
-      (!tk.empty() &&
-       hipMemcpyAsync(ev->d_tick_kind, tk.data(), tk.size(), hipMemcpyHostToDevice, st) != hipSuccess) ||
+  ev->d_tick_window = (uint32_t*)((char*)ev->d_off + off_bytes);
+  ev->d_tick_kind = (uint8_t*)((char*)ev->d_off + off_bytes + tw_bytes);
+  if (hipMemcpyAsync(ev->d_off, tables.data(), tables.size(), hipMemcpyHostToDevice, st) != hipSuccess ||
       hipStreamSynchronize(st) != hipSuccess)
     return cleanup(fail(TRE_EHIP, "copy of handle tables failed"));
 
@@ -2859,9 +2952,7 @@ extern "C" int tre_load_events(const int64_t* ts, const uint8_t* model, const ui
 extern "C" void tre_free_events(tre_events* ev) {
   if (!ev) return;
   if (ev->counted) count_handle(ev->device, -1);
-  if (ev->d_off) (void)hipFree(ev->d_off);
-  if (ev->d_tick_window) (void)hipFree(ev->d_tick_window);
-  if (ev->d_tick_kind) (void)hipFree(ev->d_tick_kind);
+  if (ev->d_off) (void)hipFree(ev->d_off);  // with the tick tables
   delete ev;
 }
 
