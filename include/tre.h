@@ -407,7 +407,9 @@ int tre_calib_workspace_size(const tre_events* ev, uint32_t req_cap, size_t* byt
    flight in LDS. A trace with more requests in flight than that table
    holds (or more than 256 FINISH rows at one instant) is redone with a
    table twice as large, and a trace that overflows that one by request-id
-   records in the workspace; after the call completes, the uint32 at byte
+   records in the workspace. A call with few long traces (at most 96, one of
+   them with at least 2^17 rows, req_cap at most that trace's rows) takes all
+   of them by records at once, with more workgroups per trace. After the call completes, the uint32 at byte
    256 of ws counts the traces redone with the larger table and the uint32
    at byte 256 + (4 + 4 * n_traces rounded up to 256) those redone by
    records (diagnostics; the results do not depend on the path).

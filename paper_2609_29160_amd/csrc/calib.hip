@@ -11,8 +11,8 @@
 // counts above the fitted boundary.
 //
 // Kernels (all on the caller's stream)
-//   fill_u32, fill_unseen  the diagnostic counts and tier lists to zero, the
-//                optional per-request records to the unseen pattern.
+//   calib_begin, fill_unseen  the diagnostic counts and tier lists at their
+//                start, the optional per-request records to the unseen pattern.
 //   calib_stream one workgroup per trace (first tier: 768 threads of two rows
 //                and a 3548-slot table; second tier: 1024 threads of four rows
 //                and twice the table, for the traces the first one lists):
@@ -24,7 +24,7 @@
 //                window's packed (judged, ok) counter) and retires its slot;
 //                a trace that overflows the table is listed for the next tier.
 //   fb_reset, calib_join, calib_judge  the chunked path for the traces the
-//                second tier lists: per-chunk LDS combining merged into
+//                second tier lists, and for few long traces at once: per-chunk LDS combining merged into
 //                16-byte id-indexed records with atomics, then one thread per
 //                record judges it. It assumes nothing about row order.
 //   calib_fit    one 1024-thread workgroup per pair of models of a trace
@@ -67,15 +67,6 @@ __device__ __forceinline__ T lds_load(const T& x) {
 }
 
 // ------------------------------------------------------------------- fill
-__global__ __launch_bounds__(256) void fill_u32(uint32_t* p, uint64_t n, uint32_t v) {
-  const uint64_t n4 = n / 4;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  uint4* q = (uint4*)p;
-  const uint4 vv = make_uint4(v, v, v, v);
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) q[i] = vv;
-  for (uint64_t i = 4 * n4 + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
-}
-
 // request slots that no ARRIVE reaches: model 0xFF, no flags, zero latencies
 __global__ __launch_bounds__(256) void fill_unseen(tre_req_latency* r, uint64_t n) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -665,6 +656,7 @@ struct FallbackParams {
   int32_t M;
   int64_t window_ms;
   int64_t n_windows;
+  uint32_t magic_w;             // as StreamParams
 };
 
 __global__ __launch_bounds__(256) void fb_reset(FallbackParams p) {
@@ -689,13 +681,27 @@ __global__ __launch_bounds__(256) void fb_reset(FallbackParams p) {
   }
 }
 
-constexpr int kHashSlots = 2048;           // LDS records per chunk (load factor about 0.4)
+// the diagnostic counts and the lists at their start: n_bad to zero, the
+// first list empty, the second one empty or (by records at once) every trace
+__global__ __launch_bounds__(256) void calib_begin(uint32_t* bad, uint32_t* l1, uint32_t* l2, uint32_t n_all) {
+  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) {
+    bad[0] = bad[1] = 0u;
+    l1[0] = 0u;
+    l2[0] = n_all;
+  }
+  if (i < n_all) l2[1 + i] = i;
+}
+
+constexpr int kHashBits = 11;
+constexpr int kHashSlots = 1 << kHashBits;  // LDS records per chunk (load factor about 0.4)
+constexpr int kJoinThreads = 256;
 constexpr int kProbes = 16;                // linear probes before the global fallback
 constexpr int kJoinBatch = 8;              // events per thread loaded together
 
 // Work items (listed trace, chunk of kJoinChunk rows), one per workgroup at
 // a time.
-__global__ __launch_bounds__(256) void calib_join(FallbackParams p) {
+__global__ __launch_bounds__(kJoinThreads) void calib_join(FallbackParams p) {
   __shared__ uint32_t h_id[kHashSlots], h_a[kHashSlots], h_f[kHashSlots], h_e[kHashSlots], h_d[kHashSlots];
   const uint64_t items = (uint64_t)p.fb[0] * p.n_chunks;
   unsigned bad = 0;
@@ -706,7 +712,7 @@ __global__ __launch_bounds__(256) void calib_join(FallbackParams p) {
     if (c0 >= e) continue;  // whole block
     const int64_t c1 = c0 + kJoinChunk < e ? c0 + kJoinChunk : e;
     uint32_t* tt = p.tab + (uint64_t)t * p.req_cap * 4;
-    for (int i = threadIdx.x; i < kHashSlots; i += 256) {
+    for (int i = threadIdx.x; i < kHashSlots; i += kJoinThreads) {
       h_id[i] = kNone;
       h_a[i] = kNone;
       h_f[i] = kNone;
@@ -714,11 +720,11 @@ __global__ __launch_bounds__(256) void calib_join(FallbackParams p) {
       h_d[i] = 0;
     }
     __syncthreads();
-    for (int64_t i0 = c0 + threadIdx.x; i0 < c1; i0 += 256 * kJoinBatch) {
+    for (int64_t i0 = c0 + threadIdx.x; i0 < c1; i0 += kJoinThreads * kJoinBatch) {
       uint32_t rr[kJoinBatch], kt[kJoinBatch], tk[kJoinBatch];
 #pragma unroll
       for (int u = 0; u < kJoinBatch; ++u) {
-        const int64_t i = i0 + 256 * u;
+        const int64_t i = i0 + kJoinThreads * u;
         const bool in = i < c1;
         rr[u] = in ? p.req[i] : kNone;
         kt[u] = in ? p.type[i] : TRE_PREFILL;
@@ -726,7 +732,7 @@ __global__ __launch_bounds__(256) void calib_join(FallbackParams p) {
       }
 #pragma unroll
       for (int u = 0; u < kJoinBatch; ++u) {
-        const int64_t i = i0 + 256 * u;
+        const int64_t i = i0 + kJoinThreads * u;
         if (i >= c1) continue;
         const uint32_t r = rr[u];
         if (r >= p.req_cap) {
@@ -736,7 +742,9 @@ __global__ __launch_bounds__(256) void calib_join(FallbackParams p) {
         const uint32_t k = kt[u] & 3u;
         if (k == TRE_PREFILL) continue;
         const uint32_t row = (uint32_t)(i - b);
-        uint32_t h = (r * 0x9E3779B1u) >> (32 - 11);
+        // neighbouring ids in neighbouring slots (their records are then
+        // flushed side by side), ids a power of two apart still spread
+        uint32_t h = (r ^ (r >> kHashBits) ^ (r >> (2 * kHashBits))) & (kHashSlots - 1);
         int slot = -1;
         for (int q = 0; q < kProbes; ++q) {
           const uint32_t old = atomicCAS(&h_id[h], kNone, r);
@@ -769,7 +777,7 @@ __global__ __launch_bounds__(256) void calib_join(FallbackParams p) {
       }
     }
     __syncthreads();
-    for (int s = threadIdx.x; s < kHashSlots; s += 256) {
+    for (int s = threadIdx.x; s < kHashSlots; s += kJoinThreads) {
       const uint32_t r = h_id[s];
       if (r == kNone) continue;
       uint32_t* rec = tt + (uint64_t)r * 4;
@@ -789,27 +797,31 @@ __global__ __launch_bounds__(256) void calib_join(FallbackParams p) {
 
 // One thread per (listed trace, request slot).
 __global__ __launch_bounds__(256) void calib_judge(FallbackParams p) {
-  const uint64_t items = (uint64_t)p.fb[0] * p.req_cap;
-  for (uint64_t it = (uint64_t)blockIdx.x * 256 + threadIdx.x; it < items; it += (uint64_t)gridDim.x * 256) {
-    const uint32_t t = p.fb[1 + it / p.req_cap], r = (uint32_t)(it % p.req_cap);
-    const uint64_t slot = (uint64_t)t * p.req_cap + r;
-    const uint4 rec = ((const uint4*)p.tab)[slot];
-    if (rec.x == kNone) continue;  // no ARRIVE: the reset left the slot unseen
-    const int64_t b = p.off[t];
-    const uint32_t m = p.model[b + rec.x];
-    tre_req_latency out = not_judged(m);
-    if (rec.y != kNone && rec.z != kNone && m < (uint32_t)p.M) {
-      const tre_slo& q = p.slo[(uint64_t)t * p.M + m];
-      const int64_t ta = p.ts[b + rec.x];
-      out = judge_one(ta, p.ts[b + rec.y], p.ts[b + rec.z], ~rec.w - (uint32_t)p.tokens[b + rec.y], m, q.ttft_ms,
-                      q.tpot_ms, q.e2e_ms);
-      const int64_t w = ta / p.window_ms;  // window of arrival
-      if (w >= 0 && w < p.n_windows)
-        atomicAdd(p.counts + ((uint64_t)t * p.M + m) * p.n_windows + w,
-                  (1u << 16) | ((out.flags & TRE_REQ_OK) ? 1u : 0u));
+  const uint32_t n_list = p.fb[0], win = (uint32_t)p.window_ms;
+  for (uint32_t pos = blockIdx.y; pos < n_list; pos += gridDim.y)
+    for (uint64_t r = (uint64_t)blockIdx.x * 256 + threadIdx.x; r < p.req_cap; r += (uint64_t)gridDim.x * 256) {
+      const uint32_t t = p.fb[1 + pos];
+      const uint64_t slot = (uint64_t)t * p.req_cap + r;
+      const uint4 rec = ((const uint4*)p.tab)[slot];
+      if (rec.x == kNone) continue;  // no ARRIVE: the reset left the slot unseen
+      const int64_t b = p.off[t];
+      const uint32_t m = p.model[b + rec.x];
+      tre_req_latency out = not_judged(m);
+      if (rec.y != kNone && rec.z != kNone && m < (uint32_t)p.M) {
+        const tre_slo& q = p.slo[(uint64_t)t * p.M + m];
+        const int64_t ta = p.ts[b + rec.x];
+        out = judge_one(ta, p.ts[b + rec.y], p.ts[b + rec.z], ~rec.w - (uint32_t)p.tokens[b + rec.y], m, q.ttft_ms,
+                        q.tpot_ms, q.e2e_ms);
+        // window of arrival, ta / window_ms: the multiply-high undershoots by at
+        // most one (ta < 2^32, window_ms <= 2^23)
+        uint32_t w = __umulhi((uint32_t)ta, p.magic_w);
+        w += (uint32_t)ta - w * win >= win ? 1u : 0u;
+        if (ta >= 0 && ta <= 0xFFFFFFFFll && w < (uint32_t)p.n_windows)
+          atomicAdd(p.counts + ((uint64_t)t * p.M + m) * p.n_windows + w,
+                    (1u << 16) | ((out.flags & TRE_REQ_OK) ? 1u : 0u));
+      }
+      if (p.reqs) p.reqs[slot] = out;
     }
-    if (p.reqs) p.reqs[slot] = out;
-  }
 }
 
 // -------------------------------------------------------------------- fit
@@ -1593,6 +1605,17 @@ static int launch_fit(const tre_events* ev, const tre_slo* slo, const double* ts
   return TRE_OK;
 }
 
+// Few long traces go by records at once: one workgroup per trace leaves most
+// of the chip idle. The stream takes 2.4 ns a row of the longest trace (up to
+// two workgroups a CU), the records 18 ps a row of every trace plus a 16-byte
+// record per id (16 traces of 6.1 M rows: 14651 / 1770 us), so the line lies
+// near 130 traces; below 2^17 rows the records' three launches show, and ids
+// far apart would cost more records than rows.
+constexpr int64_t kRecordsTraces = 96, kRecordsRows = 1 << 17;
+static bool records_first(const tre_events* ev, int64_t maxlen, uint32_t req_cap) {
+  return (int64_t)ev->n_traces <= kRecordsTraces && maxlen >= kRecordsRows && (int64_t)req_cap <= maxlen;
+}
+
 extern "C" int tre_calibrate(const tre_events* ev, const tre_slo* slo, const double* tss64,
                              const uint8_t* flags, uint32_t req_cap, uint32_t* counts, tre_fit* fit,
                              tre_req_latency* reqs, uint64_t* n_bad_ids, void* ws, size_t ws_bytes,
@@ -1621,17 +1644,17 @@ extern "C" int tre_calibrate(const tre_events* ev, const tre_slo* slo, const dou
   uint32_t* tab = (uint32_t*)((char*)ws + 256 + 2 * calib_list_bytes(ev));
   int64_t maxlen = 0;
   for (uint32_t i = 0; i < ev->n_traces; ++i) maxlen = std::max<int64_t>(maxlen, ev->h_off[i + 1] - ev->h_off[i]);
+  const bool by_records = records_first(ev, maxlen, req_cap);
+  const uint32_t n_all = by_records ? ev->n_traces : 0u;
   {
     LaunchTimer lt("calib_fill", st);
-    hipLaunchKernelGGL(fill_u32, dim3(1), dim3(256), 0, st, (uint32_t*)bad, (uint64_t)2, 0u);
-    hipLaunchKernelGGL(fill_u32, dim3(1), dim3(256), 0, st, l1, (uint64_t)1, 0u);
-    hipLaunchKernelGGL(fill_u32, dim3(1), dim3(256), 0, st, l2, (uint64_t)1, 0u);
-    if (reqs)
+    hipLaunchKernelGGL(calib_begin, dim3(n_all / 256 + 1), dim3(256), 0, st, (uint32_t*)bad, l1, l2, n_all);
+    if (reqs && !by_records)
       hipLaunchKernelGGL(fill_unseen, dim3(4096), dim3(256), 0, st, reqs, (uint64_t)ev->n_traces * req_cap);
     lt.done();
   }
   HIP_TRY(hipGetLastError());
-  if (ev->n_traces > 0) {
+  if (ev->n_traces > 0 && !by_records) {
     StreamParams sp{ev->ts, ev->model, ev->req, ev->type, ev->tokens, ev->d_off, slo, counts, reqs, bad,
                     nullptr, l1, req_cap, M, ev->cfg.window_ms, nW, window_magic(ev->cfg.window_ms)};
     LaunchTimer lt("calib_stream", st);
@@ -1643,19 +1666,21 @@ extern "C" int tre_calibrate(const tre_events* ev, const tre_slo* slo, const dou
     // the traces the first tier listed, then those the second listed (none
     // on most inputs: the launches then end at once)
     const uint32_t C = (uint32_t)((maxlen + kJoinChunk - 1) / kJoinChunk);
-    FallbackParams f1{ev->ts, ev->model, ev->req, ev->type, ev->tokens, ev->d_off, slo, counts, reqs, nullptr, bad,
-                      l1, req_cap, C, M, ev->cfg.window_ms, nW};
-    FallbackParams f2 = f1;
-    f2.tab = tab;
-    f2.fb = l2;
-    StreamParams sp{ev->ts, ev->model, ev->req, ev->type, ev->tokens, ev->d_off, slo, counts, reqs, bad,
-                    l1, l2, req_cap, M, ev->cfg.window_ms, nW, window_magic(ev->cfg.window_ms)};
+    FallbackParams f2{ev->ts, ev->model, ev->req, ev->type, ev->tokens, ev->d_off, slo, counts, reqs, tab, bad,
+                      l2, req_cap, C, M, ev->cfg.window_ms, nW, window_magic(ev->cfg.window_ms)};
     LaunchTimer lt("calib_fallback", st);
-    hipLaunchKernelGGL(fb_reset, dim3(64, 16), dim3(256), 0, st, f1);
-    hipLaunchKernelGGL((calib_stream<kBuckets2, kThreads2, kRows2>), dim3(ev->n_traces), dim3(kThreads2), 0, st, sp);
+    if (!by_records) {
+      FallbackParams f1 = f2;
+      f1.tab = nullptr;
+      f1.fb = l1;
+      StreamParams sp{ev->ts, ev->model, ev->req, ev->type, ev->tokens, ev->d_off, slo, counts, reqs, bad,
+                      l1, l2, req_cap, M, ev->cfg.window_ms, nW, window_magic(ev->cfg.window_ms)};
+      hipLaunchKernelGGL(fb_reset, dim3(64, 16), dim3(256), 0, st, f1);
+      hipLaunchKernelGGL((calib_stream<kBuckets2, kThreads2, kRows2>), dim3(ev->n_traces), dim3(kThreads2), 0, st, sp);
+    }
     hipLaunchKernelGGL(fb_reset, dim3(64, 16), dim3(256), 0, st, f2);
-    hipLaunchKernelGGL(calib_join, dim3(1024), dim3(256), 0, st, f2);
-    hipLaunchKernelGGL(calib_judge, dim3(1024), dim3(256), 0, st, f2);
+    hipLaunchKernelGGL(calib_join, dim3(1024), dim3(kJoinThreads), 0, st, f2);
+    hipLaunchKernelGGL(calib_judge, dim3(128, 16), dim3(256), 0, st, f2);
     lt.done();
     HIP_TRY(hipGetLastError());
   }
