@@ -32,6 +32,7 @@
 //                lanes). Which of several equally early slots a request
 //                takes, and where a removed slot's place goes, changes no
 //                output: only the multiset of free times matters.
+//   loop_waves   the same with 1 to 8 waves per scenario, up to 2048 scenarios.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -51,6 +52,7 @@ namespace {
 
 constexpr int kNear = 4;  // windows ahead whose tallies sit in LDS (power of two)
 constexpr int kStage = 4;  // requests per lane staged in LDS for the starts
+constexpr int kMaxWaves = 8;  // waves per scenario (loop_waves)
 constexpr int kEnt = 2;    // starts a lane records per pass of the wave's event generation
 constexpr uint32_t kNone = 0xffffffffu;
 constexpr int64_t kNever = INT64_MAX;
@@ -106,6 +108,9 @@ struct LoopParams {
   uint32_t pmagic, dmagic;      // x / chunk == umulhi(x, magic) for x < 2^16 (magic 0: chunk 1, x)
   int32_t svc32;                // every remainder chunk's tokens * us + 999 below 2^32 (declared bounds)
   int32_t r_hi;                 // min(r_cap, budget): replicas one model may hold
+  int32_t n_waves;              // loop_waves: waves of a scenario
+  int32_t gsh;                  //   log2 of half a request ring's entries
+  int32_t rec_cap;              //   starts a wave records before their events are added
   uint32_t ring_len;            // power of two above the longest span of a request in windows
   int32_t window_ms;
   int32_t duration_ms;          // duration + longest service < 2^31
@@ -795,6 +800,586 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
   if (lane == 0 && overflow) atomicAdd(p.overflow, (unsigned long long)overflow);
 }
 
+// The same replay with several waves per scenario, for calls with too few
+// scenarios to give every SIMD its waves: one wave alone is bound by its own
+// chain of instructions, about 20,000 cycles a window, not by memory (without
+// any traffic to the far rings the time falls by a tenth). Wave v serves models
+// v, v + n_waves, ..., each wave at its own pace from one tick to the next
+// (models meet only in the controller); at a tick the models' Z go through LDS,
+// one barrier, and every wave makes the same decisions. Every heap has words
+// for r_hi replicas, so moves repack nothing; the requests come through LDS
+// rings that the wave fills ahead, their service times computed there; the
+// serial turn of a start is the chain through the heap alone, events and
+// judging are added afterwards by all lanes (192 scenarios x 8 models, 7200
+// windows: rings alone 131 -> 112 ms, eight waves 78, the short turn 57).
+template <bool kAct>
+__global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(2, 8))) void loop_waves(LoopParams p) {
+  extern __shared__ __align__(16) uint32_t lds[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int n_waves = p.n_waves;
+  const uint32_t s = blockIdx.x;
+  const int M = p.M;
+  // two layouts: serving, lane l of wave v = model l * n_waves + v; the
+  // controller's state, lane = model, alike in every wave
+  const bool act = lane * n_waves + wave < M, cact = lane < M;
+  const int mc = act ? lane * n_waves + wave : 0, cm = cact ? lane : 0;
+  const tre_scenario sc = p.sc[s];
+  const uint32_t t = sc.trace < p.n_traces ? sc.trace : 0;
+  const uint64_t tm = (uint64_t)t * M + mc, ctm = (uint64_t)t * M + cm;
+  // the profile's smoothing terms stay in registers; the thresholds are
+  // read again at ticks, the SLO bounds sit in LDS
+  const double w_p = p.prof[tm].w_p, w_q = p.prof[tm].w_q, alpha = p.prof[tm].alpha;
+  const int r_init = p.prof[ctm].r_init;
+  const tre_service sv = p.svc[tm];
+  const int32_t W = p.window_ms, dur = p.duration_ms;
+  const uint32_t L = p.ring_len;
+  const int spr = p.spr;
+  const int64_t p_full = ceil_ms(p.pchunk, sv.prefill_us), d_full = ceil_ms(p.dchunk, sv.decode_us);
+  // the slot heaps, each in words for r_hi replicas' slots; the unused ones
+  // hold kNone
+  uint32_t* const hpool = lds;
+  // starts recorded for the wave's event pass: start, prompt | output << 16,
+  // arrival, model
+  uint4* const rec = (uint4*)(lds + p.pool_words) + wave * p.rec_cap;
+  uint32_t* const rest = lds + p.pool_words + 4 * n_waves * p.rec_cap;
+  double* const slo_t = (double*)rest + mc;  // ttft, tpot, e2e bounds at slo_t[i * M]
+  uint32_t* near = rest + 6 * M + mc;  // field f of ring cell c at near[(f * kNear + c) * M]
+  // each model's chunk times and rates (prompt chunk, output chunk,
+  // prefill_us, decode_us) at cst[i * M]
+  uint32_t* cst = rest + (6 + 4 * kNear) * M + mc;
+  // two rings of 2 << gsh coming requests per model, entry e of model m at
+  // (e & rmask) * Ms + m: arrivals (ms, at most the duration) for the arrival
+  // count; arrival, prompt | output << 16 and service time for the starts
+  // (which fall behind the arrivals when requests wait)
+  const int gsh = p.gsh, Ms = M | 1;
+  const uint32_t G = 1u << gsh, rmask = 2u * G - 1u;
+  int32_t* const ring_n = (int32_t*)(rest + (10 + 4 * kNear) * M);
+  int32_t* const ring_a = ring_n + 2 * G * Ms;
+  uint32_t* const ring_p = (uint32_t*)(ring_a + 2 * G * Ms);
+  uint32_t* const ring_t = ring_p + 2 * G * Ms;
+  double* const zbuf = (double*)(ring_t + 2 * G * Ms);  // Z of each model at even, at odd ticks
+  // judged requests of each model: E2E sum, count, SLO met, largest E2E
+  unsigned long long* const acc_sum = (unsigned long long*)(zbuf + 2 * M) + mc;
+  uint32_t* const acc = (uint32_t*)((unsigned long long*)(zbuf + 2 * M) + M) + mc;  // field i at acc[i * M]
+  // the far rings' cell c of this lane at index fo + c * M (one offset for
+  // the three rings keeps one register pair)
+  const uint64_t fo = (uint64_t)s * L * M + mc;
+  // initial replicas: at most r_hi per model and pool_reps in all (initial
+  // replicas within the budget and the declared bound are never cut; cut
+  // ones are counted as bounds exceeded)
+  const int r_hi = p.r_hi;
+  int R = cact ? (r_init < 0 ? 0 : (r_init > r_hi ? r_hi : r_init)) : 0;
+  unsigned slots_over = 0;  // replicas / slots the pool could not hold
+  {
+    int incl = R;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o);
+      if (lane >= o) incl += v;
+    }
+    const int room = p.pool_reps - (incl - R);
+    const int R0 = R;
+    R = R < room ? R : (room > 0 ? room : 0);
+    slots_over += (unsigned)(R0 - R);
+  }
+  // GPUs per replica (1 without the actuation model); idle GPUs (replicas)
+  // (at least 1, so that the replicas never outnumber the budget's GPUs and
+  // the heaps' pool always holds their slots)
+  const int g_in = (kAct && p.footprint && cact) ? p.footprint[ctm] : 1;
+  const int g = g_in < 1 ? 1 : g_in;
+  int rsum = R * g;
+  for (int o = 32; o > 0; o >>= 1) rsum += __shfl_xor(rsum, o);
+  int pool = p.budget - rsum;
+  // the lane's transition in flight (0 none, 1 wake, 2 sleep), the window at
+  // whose end it completes, and the GPUs a sleep returns to the idle pool
+  int tkind = 0, tuntil = 0, tret = 0;
+  int chs = R * spr;                               // heap sizes (R <= r_hi), the controller's layout
+  const int R_own = __shfl(R, mc);
+  int hs = act ? R_own * spr : 0;                  // this model's
+  const int hw = Heap::words(r_hi * spr);          // words of one heap
+  const Heap slot{hpool + mc * hw};
+  if (act) {
+    const tre_slo sl = p.slo[tm];
+    slo_t[0] = sl.ttft_ms;
+    slo_t[M] = sl.tpot_ms;
+    slo_t[2 * M] = sl.e2e_ms;
+    cst[0] = (uint32_t)p_full;
+    cst[M] = (uint32_t)d_full;
+    cst[2 * M] = sv.prefill_us;
+    cst[3 * M] = sv.decode_us;
+    acc_sum[0] = 0ull;
+    acc[0] = acc[M] = acc[2 * M] = 0u;
+    for (int i = 0; i < 4 * kNear; ++i) near[i * M] = 0u;
+    for (int i = 0; i < hw - 3; ++i) slot.at(i) = i < hs ? 0u : kNone;  // equal keys form a heap
+    for (uint32_t c = 0; c < L; ++c) {
+      far_store(&p.far_p[fo + (uint64_t)c * M], 0u);
+      far_store(&p.far_d[fo + (uint64_t)c * M], 0u);
+      far_store(&p.far_f[fo + (uint64_t)c * M], 0ull);
+    }
+  }
+  uint32_t bf = act && hs > 0 ? 0u : kNone;  // earliest slot free time (the heap's root)
+  // the donors' earliest-free slots leave their heaps, the receivers' slots,
+  // free from `from`, join (counts in the controller's layout)
+  auto change_slots = [&](int pops, int pushes, uint32_t from) {
+    pops = pops < chs ? pops : chs;
+    chs -= pops;
+    // the declared bound holds pool_reps * spr slots: pushes beyond it are
+    // dropped, in model order (in fours when spr is a multiple of 4)
+    int tot = chs, pin = pushes;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(pin, o);
+      if (lane >= o) pin += v;
+    }
+    for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o);
+    int allowed = p.pool_reps * spr - tot - (pin - pushes);
+    allowed = allowed < 0 ? 0 : (allowed > pushes ? pushes : allowed);
+    if (spr % 4 == 0) allowed &= ~3;
+    slots_over += (unsigned)(pushes - allowed);
+    pushes = allowed;
+    chs += pushes;
+    const int out = __shfl(pops, mc), in = __shfl(pushes, mc);
+    if (act) {
+      for (int q = 0; q < out; ++q) slot.pop(hs--);
+      for (int q = 0; q < in; ++q) slot.push(hs++, from);
+      bf = hs > 0 ? slot.at(0) : kNone;
+    }
+  };
+  const uint32_t wmagic = p.wmagic, pmagic = p.pmagic, dmagic = p.dmagic;
+  const int wshift = p.wshift;
+  // x / W for x < 2^31; x / prefill_chunk and x / decode_chunk for x < 2^16
+  auto win = [&](uint32_t x) { return (int32_t)(wshift < 0 ? x : __umulhi(x, wmagic) >> wshift); };
+  auto div_p = [&](uint32_t x) { return pmagic ? __umulhi(x, pmagic) : x; };
+  auto div_d = [&](uint32_t x) { return dmagic ? __umulhi(x, dmagic) : x; };
+  // a remainder chunk's time (ms): 32-bit when the declared bounds allow
+  const bool svc32 = p.svc32 != 0;
+  auto rem_ms = [&](uint32_t tok, uint32_t us) { return svc32 ? ceil_ms32(tok, us) : (uint32_t)ceil_ms(tok, us); };
+  const uint32_t udur = (uint32_t)dur;
+  // the model's requests: rq0 + [0, nq); indices below relative to rq0
+  const int64_t rq0 = act ? p.req_off[tm] : 0;
+  const int64_t rq1 = act ? p.req_off[tm + 1] : 0;
+  const uint32_t nq = rq1 > rq0 ? (uint32_t)(rq1 - rq0) : 0u;
+  uint32_t next_arr = 0, next_start = 0;
+  // The rings are filled G requests of 64 / G models at a time by the whole
+  // wave. A fill is issued once a window, where at most half a ring is left,
+  // and committed at the next window's start, so nothing waits on it; a ring
+  // that runs dry inside a window is filled on the spot. (One lane's own
+  // loads, four requests or one arrival at a time, cost a wait on memory each:
+  // most of a window's time with few scenarios.)
+  struct Fill {
+    uint32_t end = 0;             // this lane's requests below are in the ring
+    unsigned long long pend = 0;  // models whose fill is under way
+    int ml = -1;                  // this thread's share: the model's lane (-1: none), the request, its columns
+    uint32_t e = 0;
+    int64_t av = 0;
+    uint32_t pv = 0;
+  } fa, fs;
+  auto issue = [&](Fill& f, uint32_t next, bool starts) {
+    unsigned long long need = __ballot(f.end < nq && f.end - next <= G);
+    f.ml = -1;
+    f.pend = 0;
+    if (!need) return;
+    for (int q = 0; q < (64 >> gsh) && need; ++q) {
+      const int l = __ffsll((long long)need) - 1;
+      need &= need - 1ull;
+      f.pend |= 1ull << l;
+      f.ml = (lane >> gsh) == q ? l : f.ml;
+    }
+    const int src = f.ml < 0 ? 0 : f.ml;
+    const uint32_t end = (uint32_t)__shfl((int)f.end, src), n = (uint32_t)__shfl((int)nq, src);
+    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)rq0, src), hi = (uint32_t)__shfl((int)(rq0 >> 32), src);
+    f.e = end + ((uint32_t)lane & (G - 1u));
+    if (f.ml >= 0 && f.e < n && f.e >= end) {
+      const int64_t i = (int64_t)(((uint64_t)hi << 32) | lo) + f.e;
+      f.av = p.arrival[i];
+      if (starts) f.pv = (uint32_t)p.prompt[i] | (uint32_t)p.output[i] << 16;
+    } else {
+      f.ml = -1;
+    }
+  };
+  auto commit = [&](Fill& f, bool starts) {
+    if (!f.pend) return;
+    if (f.ml >= 0) {
+      const int32_t a = (int32_t)(f.av < (int64_t)dur ? (f.av > INT32_MIN ? f.av : INT32_MIN) : dur);
+      const uint32_t at = (f.e & rmask) * (uint32_t)Ms + (uint32_t)(f.ml * n_waves + wave);
+      if (starts) {
+        // the service time, here where every lane has a request
+        const uint32_t* const cl = cst + (f.ml * n_waves + wave - mc);
+        const uint32_t pt = f.pv & 0xffffu, out_tok = f.pv >> 16;
+        const uint32_t npf = div_p(pt), prem = pt - npf * (uint32_t)p.pchunk;
+        const uint32_t ndf = div_d(out_tok), drem = out_tok - ndf * (uint32_t)p.dchunk;
+        ring_a[at] = a;
+        ring_p[at] = f.pv;
+        ring_t[at] = npf * cl[0] + ndf * cl[M] + (prem ? rem_ms(prem, cl[2 * M]) : 0u) +
+                     (drem ? rem_ms(drem, cl[3 * M]) : 0u);
+      } else {
+        ring_n[at] = a;
+      }
+    }
+    if (f.pend >> lane & 1ull) f.end = nq - f.end < G ? nq : f.end + G;
+    f.pend = 0;
+  };
+  auto wave_fence = [] {  // the wave's LDS writes before its later reads
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  issue(fa, 0u, false);
+  issue(fs, 0u, true);
+  // the events of n recorded starts into the rings (PREFILL at the start of
+  // each prompt chunk, DECODE at the end of each output chunk, FINISH at the
+  // last) and their judging, a start on 4 to 16 lanes
+  unsigned overflow = 0;
+  int32_t w = 0;
+  auto add_events = [&](int n) {
+    if (n == 0) return;
+    wave_fence();
+    const int lsh = n <= 4 ? 4 : (n <= 8 ? 3 : 2);
+    for (int r = lane >> lsh; r < n; r += 64 >> lsh) {
+      const uint4 q = rec[r];
+      const uint32_t st = q.x, po = q.y;
+      const int dl = (int)q.w - mc;  // the start's model, from this lane's
+      const uint32_t* cl = cst + dl;
+      const uint32_t tp = cl[0], tdec = cl[M];
+      const uint32_t pt = po & 0xffffu, out_tok = po >> 16;
+      const uint32_t npf = div_p(pt), prem = pt - npf * (uint32_t)p.pchunk;
+      const uint32_t ndf = div_d(out_tok), drem = out_tok - ndf * (uint32_t)p.dchunk;
+      const uint32_t np = npf + (prem ? 1u : 0u), tot = np + ndf + (drem ? 1u : 0u);
+      const uint32_t t_drem = drem ? rem_ms(drem, cl[3 * M]) : 0u;
+      const uint32_t td = st + npf * tp + (prem ? rem_ms(prem, cl[2 * M]) : 0u);  // end of the prompt
+      const uint32_t tt = td + ndf * tdec + t_drem;                               // the last output chunk
+      if ((lane & ((1 << lsh) - 1)) == 0 && tt < udur) {  // FINISH: active -> gone
+        const int32_t xw = win(tt);
+        const uint32_t ahead = (uint32_t)(xw - w), ef = (uint32_t)(xw + 1) * (uint32_t)W - tt;
+        if (ahead < (uint32_t)kNear) {
+          uint32_t* nc = near + dl + (xw & (kNear - 1)) * M;
+          lds_add(nc + 2 * kNear * M, 1u);
+          lds_add(nc + 3 * kNear * M, ef);
+        } else if (ahead < L) {
+          far_add(&p.far_f[fo + (uint64_t)(xw & (L - 1)) * M + dl], (1ull << 32) | ef);
+        } else {
+          ++overflow;
+        }
+        if (out_tok) {  // judged as in the calibration sweep
+          // 32-bit differences: every time here is in [0, 2^31) (arrivals
+          // non-negative, the duration plus the longest service below 2^31)
+          const uint32_t t_first = td + (ndf ? tdec : t_drem);
+          const uint32_t first_ch = ndf ? (uint32_t)p.dchunk : drem;
+          const int32_t ttft = (int32_t)(t_first - q.z), e2e = (int32_t)(tt - q.z);
+          const int32_t after = (int32_t)(out_tok - first_ch);
+          const double* const sl = slo_t + dl;
+          bool good = (double)ttft <= sl[0] && (double)e2e <= sl[2 * M];
+          if (after > 0) good = good && (double)(int32_t)(tt - t_first) / (double)after <= sl[M];
+          __hip_atomic_fetch_add(acc_sum + dl, (unsigned long long)(int64_t)e2e, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+          lds_add(acc + dl, 1u);
+          if (good) lds_add(acc + M + dl, 1u);
+          if (e2e > 0)
+            __hip_atomic_fetch_max(acc + 2 * M + dl, (uint32_t)e2e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+      }
+      for (uint32_t j = (uint32_t)lane & ((1u << lsh) - 1u); j < tot; j += 1u << lsh) {
+        uint32_t t, tok;
+        int f;
+        if (j < np) {
+          t = st + j * tp;
+          tok = j < npf ? (uint32_t)p.pchunk : prem;
+          f = 0;
+        } else {
+          const uint32_t k = j - np;
+          if (k < ndf) {
+            t = td + (k + 1u) * tdec;
+            tok = (uint32_t)p.dchunk;
+          } else {
+            t = tt;
+            tok = drem;
+          }
+          f = 1;
+        }
+        if (t < udur) {
+          const int32_t x = win(t);
+          const uint32_t ahead = (uint32_t)(x - w);
+          if (ahead < (uint32_t)kNear) {
+            lds_add(near + dl + (f * kNear + (x & (kNear - 1))) * M, tok);
+          } else if (ahead < L) {
+            const uint64_t fcell = (uint64_t)(x & (L - 1)) * M + dl;
+            far_add(f ? &p.far_d[fo + fcell] : &p.far_p[fo + fcell], tok);
+          } else {
+            ++overflow;
+          }
+        }
+      }
+    }
+    wave_fence();
+  };
+  uint32_t fp = 0, fd = 0, fn = 0, fe = 0;  // far cell of window w - 1 + kNear, loaded at window w - 1
+  int32_t cA = 0, cW = 0;  // active / waiting requests at the current window's start
+  double S = 0.0;
+  bool init = false;
+  uint32_t n_arr = 0, n_start = 0;
+  int64_t rw = 0;
+  uint32_t nm = 0;
+  int tick = 0;  // ticks so far (wave-uniform)
+  const unsigned long long live = __ballot(cact);
+  const int lanes = (M + n_waves - 1) / n_waves;  // models of a wave, at most
+
+  int to_fast = p.fast_w, to_slow = p.slow_w;  // windows to the next tick of each cadence
+
+  for (; w < p.n_windows; ++w) {
+    const int32_t w_end = (w + 1) * W;
+    // what the last window's loads brought: requests into the rings, the far
+    // tallies of window w - 1 + kNear into LDS (one wait for both)
+    commit(fa, false);
+    commit(fs, true);
+    if (fp | fd | fn | fe) {
+      uint32_t* nc = near + ((w - 1) & (kNear - 1)) * M;
+      if (fp) lds_add(nc, fp);
+      if (fd) lds_add(nc + kNear * M, fd);
+      if (fn) lds_add(nc + 2 * kNear * M, fn);
+      if (fe) lds_add(nc + 3 * kNear * M, fe);
+      const uint64_t c0 = (uint64_t)((uint32_t)(w - 1 + kNear) & (L - 1)) * M;
+      far_store(&p.far_p[fo + c0], 0u);
+      far_store(&p.far_d[fo + c0], 0u);
+      far_store(&p.far_f[fo + c0], 0ull);
+    }
+    wave_fence();
+    if constexpr (kAct) {  // transitions that completed at the end of an earlier window
+      const bool done = tkind != 0 && tuntil < w;
+      int push = 0;
+      if (done && tkind == 1) {
+        push = R < r_hi ? spr : 0;
+        R += 1;
+      }
+      unsigned long long back = __ballot(done && tkind == 2 && tret > 0);
+      while (back) {
+        const int l = __ffsll((long long)back) - 1;
+        pool += __builtin_amdgcn_readlane(tret, l);
+        back &= back - 1ull;
+      }
+      if (done) {
+        tkind = 0;
+        tret = 0;
+      }
+      if (__ballot(push > 0)) change_slots(0, push, (uint32_t)(w * W));
+    }
+    uint32_t P = 0, D = 0;
+    int64_t eA = 0, eW = 0;
+    int32_t dA = 0, dW = 0;
+    bool idle = true;
+    // arrivals: a request waits from its arrival
+    for (;;) {
+      while (next_arr != fa.end) {
+        const int32_t a = ring_n[(next_arr & rmask) * (uint32_t)Ms + (uint32_t)mc];
+        if (a >= w_end) break;
+        eW += w_end - (int64_t)a;
+        dW += 1;
+        ++n_arr;
+        ++next_arr;
+      }
+      if (!__ballot(next_arr == fa.end && fa.end < nq)) break;
+      issue(fa, next_arr, false);
+      commit(fa, false);
+      wave_fence();
+    }
+    // ---- starts, in arrival order, on the slot that frees first: one per
+    // lane and turn (only the chain through the slots: start and finish),
+    // recorded for the wave to add their events and judge them.
+    int nrec = 0;
+    for (;;) {
+      bool go = false, dry = false;
+      int32_t a = 0, st = 0;
+      const uint32_t at = (next_start & rmask) * (uint32_t)Ms + (uint32_t)mc;
+      if (next_start != next_arr && hs > 0) {
+        if (next_start == fs.end) {
+          dry = true;
+        } else {
+          a = ring_a[at];
+          st = a > (int32_t)bf ? a : (int32_t)bf;  // a slot's free time is below 2^31
+          go = st < w_end;  // else capacity may change at the window's end
+        }
+      }
+      const unsigned long long goers = __ballot(go);
+      if (!goers) {
+        if (!__ballot(dry)) break;
+        issue(fs, next_start, true);
+        commit(fs, true);
+        wave_fence();
+        continue;
+      }
+      if (go) {
+        // admission: waiting -> active
+        eW -= w_end - st;
+        dW -= 1;
+        eA += w_end - st;
+        dA += 1;
+        const uint32_t tt = (uint32_t)st + ring_t[at];  // the last output chunk
+        bf = slot.replace_top(hs, tt);  // tt >= st >= the root
+        rec[nrec + __popcll(goers & ((1ull << lane) - 1ull))] = make_uint4((uint32_t)st, ring_p[at], (uint32_t)a, (uint32_t)mc);
+        ++n_start;
+        ++next_start;
+      }
+      nrec += __popcll(goers);
+      if (nrec > p.rec_cap - lanes) {
+        add_events(nrec);
+        nrec = 0;
+      }
+    }
+    add_events(nrec);
+    // the loads the next window's start takes in
+    if (act) {
+      const uint64_t c1 = (uint64_t)((uint32_t)(w + kNear) & (L - 1)) * M;
+      fp = far_load(&p.far_p[fo + c1]);
+      fd = far_load(&p.far_d[fo + c1]);
+      const unsigned long long ff = far_load(&p.far_f[fo + c1]);
+      fn = (uint32_t)(ff >> 32);
+      fe = (uint32_t)ff;
+    }
+    issue(fa, next_arr, false);
+    issue(fs, next_start, true);
+    if (act) {
+      {  // the window's tallies, now complete: requests started before it and in it
+        uint32_t* nc = near + (w & (kNear - 1)) * M;
+        P = nc[0];
+        D = nc[kNear * M];
+        const uint32_t nf = nc[2 * kNear * M], ef = nc[3 * kNear * M];
+        nc[0] = 0u;
+        nc[kNear * M] = 0u;
+        nc[2 * kNear * M] = 0u;
+        nc[3 * kNear * M] = 0u;
+        dA -= nf;
+        eA -= ef;
+      }
+      // the window's tallies, Eq. (1) and the smoothing
+      const int64_t A_int = (int64_t)W * cA + eA, W_int = (int64_t)W * cW + eW;  // counts below 2^31
+      cA += dA;
+      cW += dW;
+      idle = P == 0 && D == 0 && A_int == 0 && W_int == 0;
+      if (!idle) {
+        double num = w_p * (double)P;
+        num = num + (double)D;
+        num = num * 1000.0;
+        const double q = w_q * (double)W_int;
+        double den = (double)A_int + q;
+        if (den < (double)W) den = (double)W;
+        const double raw = num / den;
+        if (init) {
+          const double t1 = alpha * raw;
+          const double t2 = (1.0 - alpha) * S;
+          S = t1 + t2;
+        } else {
+          S = raw;
+          init = true;
+        }
+      }
+      if (p.tss64) p.tss64[((uint64_t)s * p.n_windows + w) * M + mc] = S;
+    }
+    rw += R;
+    // ---- tick: the controller's rules on this window's TSS
+    const bool fast = --to_fast == 0, slow = --to_slow == 0;
+    if (fast) to_fast = p.fast_w;
+    if (slow) to_slow = p.slow_w;
+    if (!fast && !slow) continue;
+    const int tk = tick++;
+    // each model's Z (Eq. (2)) to every wave; the buffers alternate, so the
+    // one barrier a tick also keeps a slow wave's reads of the last tick
+    if (act) zbuf[(tk & 1) * M + mc] = (!idle && init) ? S / (p.prof[tm].theta * sc.theta_scale) : INFINITY;
+    const tre_profile prt = p.prof[ctm];  // the thresholds, read at ticks only
+    const double tau_c = sc.tau_crit_override >= 0.0 ? sc.tau_crit_override : prt.tau_crit;
+    __syncthreads();
+    const double Z = cact ? zbuf[(tk & 1) * M + cm] : INFINITY;
+    const unsigned long long crit = __ballot(cact && Z < tau_c);
+    unsigned long long ok;
+    int path;
+    if (crit) {
+      if (!fast) continue;  // rescue pending: rebalancing defers
+      path = TRE_PATH_RESCUE;
+      ok = crit;
+    } else if (slow) {
+      path = TRE_PATH_REBALANCE;
+      ok = __ballot(cact && Z < 1.0);
+    } else {
+      continue;
+    }
+    const unsigned long long sur = __ballot(cact && Z > prt.tau_surplus);
+    // models already in a move: earlier in this tick, or (kAct) in flight
+    unsigned long long used = kAct ? __ballot(tkind != 0) : 0ull;
+    const unsigned long long veto_mask = (kAct && p.veto) ? p.veto[(uint64_t)t * p.n_ticks + tk] : 0ull;
+    int pops = 0, pushes = 0;  // this tick's slot changes of this lane (a model moves at most once per tick)
+    for (uint32_t k = 0; k < sc.max_moves; ++k) {
+      const int r = pick_lane<false>(ok & ~used & __ballot(cact && R < p.r_cap), Z, lane);  // Eq. (3)
+      if (r < 0) break;
+      const int g_r = kAct ? __builtin_amdgcn_readlane(g, r) : 1;
+      int d;
+      if (pool >= g_r) {
+        pool -= g_r;
+        d = TRE_DONOR_POOL;
+        if (kAct && lane == r) {
+          tkind = 1;
+          tuntil = w + p.wake_w;
+        }
+      } else {
+        const double Zr = lane_f64(Z, r);
+        const unsigned long long cd = __ballot(cact && R > prt.r_min && Z > Zr && (!kAct || pool >= g_r - g)) &
+                                      ~crit & ~used & ~(1ull << r) & live & ~veto_mask;
+        d = pick_lane<true>(cd & sur, Z, lane);
+        if (d < 0) d = pick_lane<true>(cd & ~sur, Z, lane);
+        if (d < 0) break;
+        used |= 1ull << d;
+        const int short_by = kAct ? g_r - __builtin_amdgcn_readlane(g, d) : 0;
+        if (short_by > 0) pool -= short_by;
+        if (lane == d && R > 0) {  // the replica's slots that free first leave
+          pops = spr;
+          R -= 1;
+        }
+        if (kAct && lane == d) {
+          tkind = 2;
+          tuntil = w + p.sleep_w;
+          tret = short_by < 0 ? -short_by : 0;
+        }
+        if (kAct && lane == r) {
+          tkind = 1;
+          tuntil = w + p.sleep_w + p.wake_w;
+        }
+      }
+      used |= 1ull << r;
+      if (!kAct && lane == r) {  // the new replica's slots, free from the window's end
+        pushes = R < r_hi ? spr : 0;
+        R += 1;
+      }
+      if (lane == 0 && wave == 0 && nm < p.move_cap) {
+        tre_move mv;
+        mv.window = (uint32_t)w;
+        mv.path = (uint8_t)path;
+        mv.receiver = (uint8_t)r;
+        mv.donor = (uint8_t)d;
+        mv.pad = 0;
+        p.moves[(uint64_t)s * p.move_cap + nm] = mv;
+      }
+      ++nm;
+    }
+    if (__ballot(pops > 0 || pushes > 0)) change_slots(pops, pushes, (uint32_t)w_end);
+  }
+  if constexpr (kAct) {  // wakes completing at the end of the last window count
+    if (tkind == 1 && tuntil < p.n_windows) R += 1;
+  }
+  if (cact && wave == 0) {
+    p.r_final[(uint64_t)s * M + lane] = R;
+    p.r_windows[(uint64_t)s * M + lane] = rw;
+  }
+  if (act) {
+    tre_loop_stats st;
+    st.n_arrived = n_arr;
+    st.n_started = n_start;
+    st.n_done = acc[0];
+    st.n_ok = acc[M];
+    st.e2e_sum = (int64_t)acc_sum[0];
+    st.e2e_max = (int64_t)acc[2 * M];
+    p.stats[(uint64_t)s * M + mc] = st;
+  }
+  if (lane == 0 && wave == 0) p.n_moves[s] = nm;
+  if (wave == 0) overflow += slots_over;  // alike in every wave
+  for (int o = 32; o > 0; o >>= 1) overflow += __shfl_xor(overflow, o);
+  if (lane == 0 && overflow) atomicAdd(p.overflow, (unsigned long long)overflow);
+}
+
 // longest service of any request allowed by the declared bounds (ms)
 int64_t max_service_ms(const tre_loop_requests* rq) {
   const int64_t np = (rq->max_prompt + rq->prefill_chunk - 1) / rq->prefill_chunk;
@@ -834,6 +1419,43 @@ int pool_words(const tre_trace_cfg* cfg, const tre_loop_requests* rq) {
 // count, its chunk times and rates
 size_t lds_bytes(const tre_trace_cfg* cfg, const tre_loop_requests* rq) {
   return ((size_t)pool_words(cfg, rq) + (size_t)(6 + 4 * kNear + 2 * kStage + 4 * kEnt + 2 + 4) * cfg->n_models) * 4;
+}
+
+// loop_waves' share of a call: the waves of a scenario (0: loop_replay), the
+// request rings, LDS. Up to 2048 waves in all (8 of 256 registers a CU; 4096
+// of 128 registers spill: 1024 scenarios x 32 models 24.1 against 21.0 ms), at
+// most kMaxWaves a scenario and one per model, where the heaps at their full
+// sizes and rings of at least 8 requests leave every scenario resident.
+// Measured, loop_replay against this: 192 scenarios x 8 models under actuation
+// 131.5 / 57.3 ms; 1024 x 32 models 36.8 / 21.0 ms; 4096 scenarios of 32 models
+// keep loop_replay (the first form of the rings, one wave each, was at 20.6 ms
+// against 18.6).
+struct WavePlan {
+  int n_waves = 0, gsh = 0, rec_cap = 0, heap_words = 0;
+  size_t bytes = 0;
+};
+WavePlan wave_plan(const tre_trace_cfg* cfg, const tre_loop_requests* rq, uint32_t n_scenarios) {
+  const int M = cfg->n_models;
+  WavePlan w;
+  if (n_scenarios > 2048) return w;
+  int n = 1;
+  while (2 * n <= kMaxWaves && 2 * n <= M && 2ull * n * n_scenarios <= 2048) n *= 2;
+  const size_t room = (size_t)kLdsMax / ((n_scenarios + 255) / 256);
+  const int64_t hw = (int64_t)Heap::words(r_hi(cfg, rq) * rq->slots_per_replica) * M;
+  const int rec_cap = std::max(2 * ((M + n - 1) / n), 64);
+  for (int gsh = 5; gsh >= 2; --gsh) {
+    const size_t words = (size_t)hw + 4 * (size_t)n * rec_cap + (size_t)(10 + 4 * kNear) * M +
+                         (size_t)8 * ((size_t)(M | 1) << gsh) + 9 * (size_t)M;
+    if (4 * words <= room) {
+      w.n_waves = n;
+      w.gsh = gsh;
+      w.rec_cap = rec_cap;
+      w.heap_words = (int)hw;
+      w.bytes = 4 * words;
+      break;
+    }
+  }
+  return w;
 }
 
 // x / d == umulhi(x, m) >> sh for x < 2^31 and 1 <= d < 2^31: with 2^(l-1) < d
@@ -927,8 +1549,11 @@ static int loop_impl(const tre_trace_cfg* cfg, uint32_t n_traces, const tre_loop
   uint32_t* far_d = (uint32_t*)(base + 256 + cells * 4);
   unsigned long long* far_f = (unsigned long long*)(base + 256 + cells * 8);
   uint32_t* scratch = (uint32_t*)(base + 256 + cells * 16);
-  const size_t lds = lds_bytes(cfg, rq);
-  const void* kern = act ? (const void*)loop_replay<true> : (const void*)loop_replay<false>;
+  const WavePlan wp = wave_plan(cfg, rq, n_scenarios);
+  const bool waves = wp.n_waves > 0;
+  const size_t lds = waves ? wp.bytes : lds_bytes(cfg, rq);
+  const void* kern = waves ? (act ? (const void*)loop_waves<true> : (const void*)loop_waves<false>)
+                           : (act ? (const void*)loop_replay<true> : (const void*)loop_replay<false>);
   HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   hipLaunchKernelGGL(zero_u64, dim3(1), dim3(1), 0, st, overflow);
   LoopParams lp{};
@@ -960,9 +1585,12 @@ static int loop_impl(const tre_trace_cfg* cfg, uint32_t n_traces, const tre_loop
   lp.r_cap = rq->r_cap;
   lp.pchunk = rq->prefill_chunk;
   lp.dchunk = rq->decode_chunk;
-  lp.pool_words = pool_words(cfg, rq);
+  lp.pool_words = waves ? wp.heap_words : pool_words(cfg, rq);
   lp.pool_reps = pool_reps(cfg, rq);
   lp.r_hi = r_hi(cfg, rq);
+  lp.n_waves = wp.n_waves;
+  lp.gsh = wp.gsh;
+  lp.rec_cap = wp.rec_cap;
   magic31(cfg->window_ms, &lp.wmagic, &lp.wshift);
   lp.pmagic = magic16(rq->prefill_chunk);
   lp.dmagic = magic16(rq->decode_chunk);
@@ -986,7 +1614,11 @@ static int loop_impl(const tre_trace_cfg* cfg, uint32_t n_traces, const tre_loop
     lp.n_ticks = nt;
   }
   LaunchTimer lt("loop_replay", st);
-  if (act)
+  if (waves && act)
+    hipLaunchKernelGGL(loop_waves<true>, dim3(n_scenarios), dim3(64 * wp.n_waves), lds, st, lp);
+  else if (waves)
+    hipLaunchKernelGGL(loop_waves<false>, dim3(n_scenarios), dim3(64 * wp.n_waves), lds, st, lp);
+  else if (act)
     hipLaunchKernelGGL(loop_replay<true>, dim3(n_scenarios), dim3(64), lds, st, lp);
   else
     hipLaunchKernelGGL(loop_replay<false>, dim3(n_scenarios), dim3(64), lds, st, lp);
