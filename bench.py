@@ -507,7 +507,8 @@ def calibrate_main(args, w, dt, device, tre, torch, np):
     alg = {"tss_stream": ALG_BYTES_PER_EVENT * dt.n_events + 9 * cells,
            "calib_fill": 0,
            "calib_stream": 16 * dt.n_events + 12 * cells,
-           "calib_fallback": 0,
+           # few long traces go by records at once and skip the stream
+           "calib_fallback": 0 if kms["calib_stream"] > 0 else 16 * dt.n_events + 12 * cells,
            "calib_fit": 13 * cells}
     kernels = {k: {"ms": round(kms[k], 4), "alg_bytes": alg[k],
                    "gbs": round(alg[k] / (kms[k] / 1e3) / 1e9, 1) if kms[k] > 0 else None} for k in CALIB_KERNELS}

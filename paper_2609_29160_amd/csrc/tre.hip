@@ -2107,6 +2107,7 @@ struct ValParams {
   const uint8_t* type;
   const int64_t* off;
   const uint64_t* sub_off;   // [n_traces + 1] pieces of the traces before each
+  int64_t sub_rows;          // rows of a piece
   uint32_t n_traces;
   int64_t duration_ms;
   int64_t window_ms;
@@ -2119,9 +2120,11 @@ struct ValParams {
 };
 
 // A trace's rows in pieces of kSubRows, one wave each: few traces then still
-// fill the chip (4 traces of 1.9 M rows are 3760 waves).
+// fill the chip (4 traces of 1.9 M rows are 3760 waves). Pieces double until
+// at most kMaxSubs (and one per trace) are left, which bounds the memory of
+// their counts (8 bytes a model each) and still fills every SIMD.
 constexpr int kSubRows = 2048;
-constexpr int kValChunk = 4 * kSubRows;  // rows of one workgroup of the load-time checks
+constexpr uint64_t kMaxSubs = 16384;
 
 // One pass over the rows: order, schema and per-window range of each row, the
 // net change of each model's active and waiting counts over each piece (for
@@ -2134,9 +2137,9 @@ __global__ __launch_bounds__(256) void validate(ValParams p) {
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
   for (uint32_t t = blockIdx.y; t < p.n_traces; t += gridDim.y) {
     const int64_t b = p.off[t], e = p.off[t + 1];
-    const int64_t c0 = b + (int64_t)blockIdx.x * kValChunk + (int64_t)wv * kSubRows;
+    const int64_t c0 = b + ((int64_t)blockIdx.x * 4 + wv) * p.sub_rows;
     if (c0 >= e) continue;  // whole wave; the waves share no barrier
-    const int64_t c1 = c0 + kSubRows < e ? c0 + kSubRows : e;
+    const int64_t c1 = c0 + p.sub_rows < e ? c0 + p.sub_rows : e;
     unsigned long long* const net = s_net[wv];
     net[lane] = 0ull;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -2187,15 +2190,15 @@ __global__ __launch_bounds__(256) void validate(ValParams p) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint64_t so = p.sub_off[t], n_sub = p.sub_off[t + 1] - so;
-    if (lane < p.M) p.net[so * p.M + (uint64_t)lane * n_sub + (uint64_t)((c0 - b) / kSubRows)] = net[lane];
+    const uint64_t so = p.sub_off[t], n_sub = p.sub_off[t + 1] - so, sub = (uint64_t)blockIdx.x * 4 + wv;
+    if (lane < p.M) p.net[so * p.M + (uint64_t)lane * n_sub + sub] = net[lane];
     if (p.req) {
       for (int d = 32; d >= 1; d >>= 1) {
         const uint32_t oa = (uint32_t)__shfl_xor((int)mxa, d), ol = (uint32_t)__shfl_xor((int)mxl, d);
         mxa = oa > mxa ? oa : mxa;
         mxl = ol > mxl ? ol : mxl;
       }
-      if (lane == 0) p.sub_max[so + (uint64_t)((c0 - b) / kSubRows)] = make_uint2(mxa, mxl);
+      if (lane == 0) p.sub_max[so + sub] = make_uint2(mxa, mxl);
     }
   }
 }
@@ -2271,6 +2274,7 @@ struct StateParams {
   const uint8_t* type;
   const int64_t* off;
   const uint64_t* sub_off;
+  int64_t sub_rows;
   const unsigned long long* net;
   uint32_t n_traces;
   int32_t M;
@@ -2298,8 +2302,8 @@ __global__ __launch_bounds__(256) void validate_state(StateParams p) {
     const int64_t b = p.off[t];
     const int n = (int)(p.off[t + 1] - b);  // below 2^27
     const int sub = (int)blockIdx.x * 4 + wv;
-    if (sub * (int64_t)kSubRows >= n) continue;  // whole wave; the waves share no barrier
-    const int r_begin = sub * kSubRows, r_end = r_begin + kSubRows < n ? r_begin + kSubRows : n;
+    if (sub * p.sub_rows >= n) continue;  // whole wave; the waves share no barrier
+    const int r_begin = (int)(sub * p.sub_rows), r_end = r_begin + p.sub_rows < n ? (int)(r_begin + p.sub_rows) : n;
     const uint64_t so = p.sub_off[t], n_sub = p.sub_off[t + 1] - so;
     const unsigned long long before = lane < p.M ? p.net[so * p.M + (uint64_t)lane * n_sub + (uint64_t)sub] : 0ull;
     ca[lane] = net_a(before);
@@ -2735,10 +2739,12 @@ static int validate_events(const tre_events* ev, hipStream_t st) {
   h.err = 0;
   h.pad = 0;
   h_sub[0] = 0;
+  int64_t sub_rows = kSubRows;
+  while ((uint64_t)(ev->n_events / sub_rows) > kMaxSubs) sub_rows *= 2;
   for (uint32_t i = 0; i < n_traces; ++i) {
     const int64_t len = ev->h_off[i + 1] - ev->h_off[i];
     maxlen = std::max(maxlen, len);
-    h_sub[i + 1] = h_sub[i] + (uint64_t)((len + kSubRows - 1) / kSubRows);
+    h_sub[i + 1] = h_sub[i] + (uint64_t)((len + sub_rows - 1) / sub_rows);
   }
   if (maxlen == 0) return TRE_OK;
   const uint64_t net_bytes = h_sub[nt] * (uint64_t)c.n_models * 8;
@@ -2754,9 +2760,9 @@ static int validate_events(const tre_events* ev, hipStream_t st) {
            hipStreamSynchronize(st) == hipSuccess;
   };
   bool ok = hipMemcpyAsync(d, host.data(), net_at, hipMemcpyHostToDevice, st) == hipSuccess;
-  const dim3 grid((unsigned)((maxlen + kValChunk - 1) / kValChunk), std::min<uint32_t>(n_traces, 65535u));
+  const dim3 grid((unsigned)((maxlen + 4 * sub_rows - 1) / (4 * sub_rows)), std::min<uint32_t>(n_traces, 65535u));
   if (ok) {
-    ValParams vp{ev->ts, ev->model, ev->req, ev->type, ev->d_off, d_sub, n_traces, c.duration_ms, c.window_ms,
+    ValParams vp{ev->ts, ev->model, ev->req, ev->type, ev->d_off, d_sub, sub_rows, n_traces, c.duration_ms, c.window_ms,
                  c.n_models, max_events_per_window(c.window_ms), &d->err, d->first, d_net, d_smax};
     LaunchTimer lt("validate", st);
     hipLaunchKernelGGL(validate, grid, dim3(256), 0, st, vp);
@@ -2766,7 +2772,7 @@ static int validate_events(const tre_events* ev, hipStream_t st) {
   if (ok) {
     hipLaunchKernelGGL(net_scan, dim3(std::min<uint32_t>(n_traces, 65535u), (unsigned)(c.n_models / 4 + 1)), dim3(256), 0, st, d_net, d_sub, n_traces,
                        c.n_models, d_smax, d_admit, d_admit + nt);
-    StateParams sp{ev->ts, ev->model, ev->type, ev->d_off, d_sub, d_net, n_traces, c.n_models, &d->err,
+    StateParams sp{ev->ts, ev->model, ev->type, ev->d_off, d_sub, sub_rows, d_net, n_traces, c.n_models, &d->err,
                    &d->first[kValState]};
     hipLaunchKernelGGL(validate_state, grid, dim3(256), 0, st, sp);
     ok = hipGetLastError() == hipSuccess;
