@@ -64,8 +64,12 @@ constexpr int kLdsMax = 160 * 1024;
 // per output chunk) and the prompt tokens of PREFILL events in 4-byte cells,
 // so that one window's cells of 32 models share one cache line and the few
 // dozen windows a scenario is adding into stay in L2; its FINISH events in
-// 8-byte cells, count << 32 plus the sum of (window end - finish time) (below
-// 2^32, as the LDS ring's 32-bit cell), one add per finishing request.
+// 8-byte cells, count << 32 plus the sum of (window end - finish time), one add
+// per finishing request. That sum stays below 2^32, as in the LDS ring's 32-bit
+// cells, because only requests on a slot since an earlier window get there: one
+// a slot (so while a model's slots times the window stay below it). Finishes inside the window of their start are not bounded so (5 s
+// requests on 128 slots pass 2^32 ms in a 20-minute window) and go to the 64-bit
+// sums of the lane instead.
 
 struct LoopParams {
   const int64_t* arrival;
@@ -1049,7 +1053,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
       if ((lane & ((1 << lsh) - 1)) == 0 && tt < udur) {  // FINISH: active -> gone
         const int32_t xw = win(tt);
         const uint32_t ahead = (uint32_t)(xw - w), ef = (uint32_t)(xw + 1) * (uint32_t)W - tt;
-        if (ahead < (uint32_t)kNear) {
+        if (ahead == 0u) {
+          // in the window of its start: counted at the start, in 64 bits
+        } else if (ahead < (uint32_t)kNear) {
           uint32_t* nc = near + dl + (xw & (kNear - 1)) * M;
           lds_add(nc + 2 * kNear * M, 1u);
           lds_add(nc + 3 * kNear * M, ef);
@@ -1111,10 +1117,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     wave_fence();
   };
   uint32_t fp = 0, fd = 0, fn = 0, fe = 0;  // far cell of window w - 1 + kNear, loaded at window w - 1
-  int32_t cA = 0, cW = 0;  // active / waiting requests at the current window's start
+  int32_t cA = 0;  // active requests at the current window's start
   double S = 0.0;
   bool init = false;
-  uint32_t n_arr = 0, n_start = 0;
   int64_t rw = 0;
   uint32_t nm = 0;
   int tick = 0;  // ticks so far (wave-uniform)
@@ -1162,7 +1167,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
     }
     uint32_t P = 0, D = 0;
     int64_t eA = 0, eW = 0;
-    int32_t dA = 0, dW = 0;
+    int32_t dA = 0;
+    const uint32_t queued = next_arr - next_start;  // waiting at the window's start
     bool idle = true;
     // arrivals: a request waits from its arrival
     for (;;) {
@@ -1170,8 +1176,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         const int32_t a = ring_n[(next_arr & rmask) * (uint32_t)Ms + (uint32_t)mc];
         if (a >= w_end) break;
         eW += w_end - (int64_t)a;
-        dW += 1;
-        ++n_arr;
         ++next_arr;
       }
       if (!__ballot(next_arr == fa.end && fa.end < nq)) break;
@@ -1205,15 +1209,14 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         continue;
       }
       if (go) {
-        // admission: waiting -> active
+        // admission: waiting -> active, and gone again at a FINISH in this window
         eW -= w_end - st;
-        dW -= 1;
-        eA += w_end - st;
-        dA += 1;
         const uint32_t tt = (uint32_t)st + ring_t[at];  // the last output chunk
+        const uint32_t left = tt < (uint32_t)w_end ? tt : (uint32_t)w_end;
+        eA += left - (uint32_t)st;
+        dA += tt < (uint32_t)w_end ? 0 : 1;
         bf = slot.replace_top(hs, tt);  // tt >= st >= the root
         rec[nrec + __popcll(goers & ((1ull << lane) - 1ull))] = make_uint4((uint32_t)st, ring_p[at], (uint32_t)a, (uint32_t)mc);
-        ++n_start;
         ++next_start;
       }
       nrec += __popcll(goers);
@@ -1248,9 +1251,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
         eA -= ef;
       }
       // the window's tallies, Eq. (1) and the smoothing
-      const int64_t A_int = (int64_t)W * cA + eA, W_int = (int64_t)W * cW + eW;  // counts below 2^31
+      const int64_t A_int = (int64_t)W * cA + eA, W_int = (int64_t)W * queued + eW;  // counts below 2^31
       cA += dA;
-      cW += dW;
       idle = P == 0 && D == 0 && A_int == 0 && W_int == 0;
       if (!idle) {
         double num = w_p * (double)P;
@@ -1366,8 +1368,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) __attribute__((amdgpu_waves_per_eu(
   }
   if (act) {
     tre_loop_stats st;
-    st.n_arrived = n_arr;
-    st.n_started = n_start;
+    st.n_arrived = next_arr;
+    st.n_started = next_start;
     st.n_done = acc[0];
     st.n_ok = acc[M];
     st.e2e_sum = (int64_t)acc_sum[0];

@@ -66,3 +66,28 @@ def test_starts_beyond_the_rings(lib):
     """More arrivals and starts of one model in a 5 s window than a ring holds."""
     _run(lib, 2, 3, 200, rate=12.0, window_ms=5000, spr=64)
     _run(lib, 20, 600, 40, rate=12.0, window_ms=5000, spr=32, r_cap=8)
+
+
+@pytest.mark.parametrize("minutes,M,n_sc,act", [(20, 8, 4, False), (30, 8, 4, True), (30, 3, 4, False), (30, 1, 2049, True)])
+def test_long_windows(lib, minutes, M, n_sc, act):
+    """One model's finishes of one window, each up to minutes before its end,
+    sum to more than 32 bits hold: with several waves, with one wave a scenario,
+    and (2049 scenarios) in the kernel for many scenarios."""
+    W = minutes * 60_000
+    w = tg.standard(1).scaled(name=f"long-{minutes}min-{M}", model_classes=["7B"] * M, interactive=[m % 2 == 0 for m in range(M)],
+                              r_init=[4] * M, budget=4 * M, rate=[9.0] * M, prompt_mu=[5.0] * M, out_mu=[3.5] * M, process="poisson",
+                              duration_ms=2 * W, window_ms=W, fast_period_ms=W, slow_period_ms=W)
+    tables = [w.requests(0)]
+    a = np.asarray(tables[0]["arrival_ms"])
+    # a request is done within a minute of its arrival at this load
+    te = np.maximum(W - a % W - 60_000, 0) * (a < W)
+    assert max(int(te[tables[0]["model"] == m].sum()) for m in range(M)) > 1 << 32
+    rng = np.random.default_rng(minutes + M)
+    cfg = dict(w.trace_cfg())
+    model = None
+    if act:
+        fp, veto = L._act_model(rng, 1, M, L._n_ticks(cfg))
+        cfg["budget"] = int(4 * fp.sum()) + 3
+        model = (1310, 1870, fp, veto)
+    L._check(lib, w.name, cfg, tables, w.profile_columns(1), w.slo_columns(1), w.service_columns(1),
+             L._scenarios(rng, n_sc, 1, ks=(1, 2, 4, 0)), act=model)
