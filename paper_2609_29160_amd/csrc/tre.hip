@@ -611,9 +611,10 @@ __device__ __forceinline__ void tick_order(uint32_t* recv, uint32_t* don, uint32
   if (in && sub == 0) *head = w | (path << 30);
   if (!__ballot(in && path != 0u)) return;
   uint32_t rank = 0, p = 0, q = 0;  // models with a smaller Z; receivers and donors before this lane's model
-  // Z >= 0 and never NaN, so its bit pattern orders like its value; zs holds
-  // the wave's own words (its LDS operations stay in order)
-  const unsigned long long zm = dbits(Z);
+  // Z >= 0 or NaN. The bit patterns order like the values; a NaN, which is no
+  // receiver, takes the lowest, so that its rank lies above no receiver's and it
+  // never gives. zs holds the wave's own words (its LDS operations stay in order)
+  const unsigned long long zm = Z == Z ? dbits(Z) : 0ull;
   const uint32_t nsur = sur ? 0u : 1u;
   zs[lane] = zm;
   __builtin_amdgcn_wave_barrier();
@@ -1291,8 +1292,9 @@ __device__ __forceinline__ void stream_body(const StreamParams& p) {
             double* const rw = p.raw + ((int64_t)trace * M + rm) * 2 * nWt + w;
             rw[0] = rp;
             rw[nWt] = rd;
-            if (rp >= 0.0 && (uint32_t)w < s_first[2 * rm]) atomicMin(&s_first[2 * rm], (uint32_t)w);
-            if (rd >= 0.0 && (uint32_t)w < s_first[2 * rm + 1]) atomicMin(&s_first[2 * rm + 1], (uint32_t)w);
+            // not idle: also a NaN (infinite tokens over infinite demand)
+            if (!(rp < 0.0) && (uint32_t)w < s_first[2 * rm]) atomicMin(&s_first[2 * rm], (uint32_t)w);
+            if (!(rd < 0.0) && (uint32_t)w < s_first[2 * rm + 1]) atomicMin(&s_first[2 * rm + 1], (uint32_t)w);
           } else {
             st_p[(k % nbuf) * C * M + rj * M + rm] = rp;
             st_d[(k % nbuf) * C * M + rj * M + rm] = rd;
@@ -1615,6 +1617,10 @@ __device__ __forceinline__ double chain_rows(double* t, int plane, int str, int 
   return S;
 }
 
+// t1 of an idle window: -0.0, which no other window has (alpha * raw of a raw
+// ratio >= 0 is +0.0 or more, or a NaN of either sign)
+__device__ __forceinline__ bool idle_t1(double t1) { return dbits(t1) == 1ull << 63; }
+
 // One workgroup per trace, waves of four kinds that meet at one barrier per
 // step of `chunk` windows. A column is a model (kStage: a model's prefill or
 // decode share). In step k
@@ -1808,7 +1814,7 @@ __global__ __launch_bounds__(chain_threads(kRows), kRows ? 7 : 5) void chain_smo
           const int w = (int)(tw & 0x3FFFFFFFu);
           const int u = in ? w - w0 : 0;
           const double t1 = b[u * str + ms], Sw = b[plane + u * str + ms];
-          const bool dead = __double_as_longlong(t1) < 0 || w < fst || fst < 0;  // idle, or not initialised
+          const bool dead = idle_t1(t1) || w < fst || fst < 0;  // idle, or not initialised
           if (ctl_s >= 0) {
             const double Z = in && sub < M && !dead ? Sw / th : INFINITY;  // Eq. (2)
             const int e = in ? i : 0;
@@ -1828,7 +1834,7 @@ __global__ __launch_bounds__(chain_threads(kRows), kRows ? 7 : 5) void chain_smo
           if (p.tss64) p.tss64[o + i] = Sw;
           if (p.tss32) p.tss32[o + i] = (float)Sw;
           if (!kStage && p.flags) {
-            const bool idle = __double_as_longlong(t1) < 0, init = (uint32_t)(w0 + u) >= s_first[col];
+            const bool idle = idle_t1(t1), init = (uint32_t)(w0 + u) >= s_first[col];
             p.flags[o + i] = (uint8_t)((idle ? TRE_FLAG_IDLE : 0) | (init ? TRE_FLAG_INIT : 0));
           }
         }
@@ -1836,7 +1842,7 @@ __global__ __launch_bounds__(chain_threads(kRows), kRows ? 7 : 5) void chain_smo
           const int64_t of = ((int64_t)trace * nW + w0) * M;
           for (int i = l; i < n * M; i += kChainIO) {
             const int u = (int)(((uint32_t)(2 * i) * p.magic_k) >> 20), col = 2 * (i - u * M);
-            const bool pi = __double_as_longlong(b[u * str + col]) < 0, di = __double_as_longlong(b[u * str + col + 1]) < 0;
+            const bool pi = idle_t1(b[u * str + col]), di = idle_t1(b[u * str + col + 1]);
             const uint32_t w = (uint32_t)(w0 + u);
             p.flags[of + i] = (uint8_t)((pi ? TRE_STAGE_P_IDLE : 0) |
                                         (w >= s_first[col] ? TRE_STAGE_P_INIT : 0) |

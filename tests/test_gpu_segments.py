@@ -8,6 +8,7 @@ than models, and the number of scenarios at which the replay changes kernels.
 Every per-cell output, decision and replica sum equals the oracle's bit for
 bit. A sweep captured in a graph takes no scratch of the library's pool; its
 replays equal the eager call."""
+import edge_traces as E
 import numpy as np
 import pytest
 
@@ -106,3 +107,77 @@ def test_captured_sweep(lib):
             assert torch.equal(got[k], ref[k]), k
         assert torch.equal(g32.view(torch.int32), t32.view(torch.int32))
     ev.close()
+
+
+def _same(got, ref, what):
+    """Equal bit for bit, any NaN equal to any other."""
+    got, ref = np.asarray(got), np.asarray(ref)
+    ok = (got == ref) | (np.isnan(got) & np.isnan(ref)) if ref.dtype.kind == "f" else got == ref
+    assert ok.all(), f"{what}: {np.argwhere(~ok)[:5]}"
+
+
+@pytest.mark.parametrize("M,n_sc", [(6, 40), (20, 40), (6, 1)])
+def test_overflowing_weights(lib, M, n_sc):
+    """Weights of 1e306 (finite, so accepted): numerator and demand overflow to
+    infinity, alone and together, so ratios are +inf and NaN. A NaN share is
+    not an idle window, it counts as initialised, and its model neither
+    receives nor gives. Shares, flags and decisions as the oracle's."""
+    tre, device, torch = lib
+    import oracle as O
+    w = _workload(M, 300, 1, 500, 77, 2, 4)
+    h = w.generate(0, 1).trace(0)
+    # a request that waits in the first window of model 0 and is admitted there,
+    # then the trace a second later
+    n = int(np.searchsorted(h["ts"], 149_000))
+    head = E._pack([(0, 0, 1 << 20, 0, 0), (400, 0, 1 << 20, 0x81, 500), (450, 0, 1 << 20, 2, 9), (480, 0, 1 << 20, 3, 0)])
+    h = {k: np.concatenate([head[k], (v[:n] + 1000) if k == "ts" else v[:n]]) for k, v in h.items()}
+    cols, off = P._columns_from_host(torch, [h])
+    cfg = dict(w.trace_cfg(), budget=int(np.sum(w.r_init)))  # nothing idle: moves need donors
+    ev = tre.tre_load_events(cols["ts"], cols["model"], cols["req"], cols["type"], cols["tokens"], off, cfg)
+    pc = {k: np.array(v, copy=True) for k, v in w.profile_columns(1).items()}
+    for m, big in ((0, ("w_p", "w_q")), (2, ("w_p",)), (4, ("w_q",)), (3, ("w_p", "w_q"))):  # requests wait for model 3
+        for k in big:
+            pc[k][m] = 1e306
+    pc["r_min"][:] = 0
+    prof = tre.pack(pc, tre.PROFILE_DTYPE)
+    sc_cols = P._random_scenarios(1, n_sc, 4)
+    sc_cols["theta_scale"] = np.random.default_rng(9).uniform(1.0, 60.0, n_sc)
+    sc_cols["max_moves"][:] = 8
+    sc = tre.pack(sc_cols, tre.SCENARIO_DTYPE)
+    tre.tre_check_params(ev, prof, sc)
+    o, op = O.get(), O.pack_profiles(pc)
+    ref = o.tss_trace(h, cfg["window_ms"], cfg["duration_ms"], op)
+    assert np.isnan(ref["S"]).any() and np.isinf(ref["S"]).any()
+    g = {k: v.cpu().numpy()[0] for k, v in _eval(tre, ev, prof).items()}
+    _same(g["flags"], ref["flags"], "flags")
+    _same(g["tss64"], ref["S"], "shares")
+    st = tre.stage_outputs(ev)
+    tre.tre_eval_stage(ev, prof, st)
+    rs = o.stage_tss(ref, cfg["window_ms"], op)
+    _same(st["stage64"].cpu().numpy()[0], rs["S"], "stage shares")
+    _same(st["flags"].cpu().numpy()[0], rs["flags"], "stage flags")
+    cap = ev.n_ticks * 8
+    outs = {"rebalance": tre.ctl_outputs(ev, n_sc, cap), "sweep": tre.ctl_outputs(ev, n_sc, cap)}
+    tre.tre_rebalance(ev, prof, torch.from_numpy(ref["S"][None].copy()).cuda(), torch.from_numpy(ref["flags"][None].copy()).cuda(),
+                      sc, outs["rebalance"])
+    tre.tre_sweep(ev, prof, sc, outs["sweep"], torch.empty(tre.tre_workspace_size(ev, n_sc), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    total = 0
+    for s in range(n_sc):
+        row = np.zeros(1, O.SCENARIO_DTYPE)
+        for k in O.SCENARIO_DTYPE.names:
+            row[k] = sc_cols[k][s]
+        rc = o.control(cfg, op, ref["S"], ref["flags"], row, cap)
+        total += int((rc["moves"]["donor"] != 0xFF).sum())
+        for how, out in outs.items():
+            mv = tre.unpack_moves(out["moves"]).reshape(-1)[s * cap:(s + 1) * cap]
+            PT.compare_ctl(mv, int(out["n_moves"][s]), out["r_final"][s].cpu().numpy(), out["r_windows"][s].cpu().numpy(), rc,
+                           f"{how} scenario {s}")
+    assert total > 0
+    ev.close()
+
+
+def _eval(tre, ev, prof):
+    out = tre.tss_outputs(ev, which=("tss64", "flags"))
+    tre.tre_eval_tss(ev, prof, out)
+    return out
