@@ -2668,19 +2668,10 @@ static int stream_waves(uint32_t n_traces) {
 // The segmented path: about kSegGrid workgroups in all, at most kSegMax
 // segments a trace (every workgroup adds up the net changes of the segments
 // before its own), each a whole number of evaluation chunks; workgroups of 16
-// waves while they are at most kSegWide.
-// It costs 2 bytes a row and 16 bytes a cell more than one workgroup per
-// trace, and wins where those leave the chip idle: up to kSegTraces traces
-// (kSegStage for the stage shares, which have no workgroups above 4 waves).
-// Up to kSegSparse it still wins where a workgroup's step is bound by its
-// chunk of windows, not by its tile of rows (measured, one workgroup per trace
-// against segments: 500 traces x 32 models x 250 ms windows, 0.3 tiles a
-// chunk, 2876 / 1733 us; 768 of them, 0.6 tiles, 3275 / 2599; 401 x 13 models
-// x 200 ms, 1.4 tiles, 1698 / 1430; 300 x 16 models x 500 ms, 2.1 tiles, 1062 /
-// 1144; 768 x 8 models x 500 ms, 4.2 tiles, 580 / 1019; 200 x 8 models x 500 ms,
-// 2.1 tiles, 387 / 460; 128 x 8 models x 1 s, 4.2 tiles, 1345 / 1165).
+// waves while they are at most kSegWide. It costs three launches, 2 bytes a row
+// and 16 bytes a cell more than one workgroup per trace (seg_pays).
 constexpr size_t kSegScratchMax = 1ull << 30;
-constexpr int64_t kSegTraces = 160, kSegStage = 384, kSegSparse = 768, kSegGrid = 2048, kSegMax = 256, kSegWide = 512;
+constexpr int64_t kSegGrid = 2048, kSegMax = 256, kSegWide = 512;
 
 static size_t stream_lds(const tre_events* ev, bool stage = false) {
   const size_t M = (size_t)ev->cfg.n_models, C = (size_t)chunk_windows(ev->cfg.n_models, ev->wcap);
@@ -3082,15 +3073,45 @@ struct SegPlan {
   size_t raw = 0, net = 0, row = 0, first = 0, bytes = 0;  // offsets of the scratch arrays, total
 };
 
-SegPlan seg_plan(const tre_events* ev, bool stage) {
+// Whether segments beat one workgroup per trace. They do where those leave the
+// chip idle and the trace has steps enough to pay for three launches instead of
+// one. `cells`: per-cell outputs, which one workgroup per trace writes from its
+// serial chain. C: windows of a chunk, the step's evaluation. Measured, one
+// workgroup per trace / segments in us, 323 shapes:
+// - below four chunks (three for the stage shares) or 40 windows the launches
+//   cost more: 1 model x 40 windows 38 / 48, 32 x 10 windows 39 / 59 (160
+//   traces), x 20 windows 35 / 45; 1 model x 160 windows 60 / 43;
+// - few traces: up to 160 segments win at up to 16 models (160 traces x 8 models x
+//   500 ms 999 / 639; 128 x 8 x 1 s 1434 / 968); above, the chain is a lane per
+//   column and the line lies lower (64 x 64 models x 1 s 121 / 103; 160 x 64
+//   108 / 118, 160 x 32 46 / 56). The stage shares have no workgroups above 4
+//   waves: up to 384 (384 x 64 models 584 / 526);
+// - more traces: one workgroup per trace is bound by its chunks of windows while
+//   rows are few, and by the rows' tallies, which segments do not make cheaper,
+//   when they are many. What counts is the rows of one chunk over all traces: up
+//   to 1.0 M (768 traces: 0.96 M 805 / 650, 1.16 M 564 / 588, 1.7 M 418 / 568;
+//   500: 1.06 M 420 / 508; 250: 0.83 M 1212 / 659, 1.31 M 372 / 393), to 1.15 M in
+//   long calls with per-cell outputs (401 x 13 models, 4500 windows, 1.05 M,
+//   under actuation 1712 / 1421; without outputs 1121 / 1390), to 1.8 M from 257
+//   to 384 traces, whose 16-wave workgroups take two rounds (1.7 M 512 / 416,
+//   2.2 M 382 / 462). Stage shares: 1.5 tiles a chunk and trace.
+bool seg_pays(const tre_events* ev, bool stage, bool cells) {
+  constexpr int64_t kFew = 160, kFewWide = 96, kFewStage = 384, kMost = 768;
+  const int64_t T = ev->n_traces, M = ev->cfg.n_models, nW = ev->n_windows, C = chunk_windows((int)M, ev->wcap);
+  if ((nW + C - 1) / C < (stage ? 3 : 4) || (!stage && nW < 40)) return false;
+  if (T <= (stage ? kFewStage : M <= kChainRows ? kFew : kFewWide)) return true;
+  if (T > kMost) return false;
+  const double chunk_rows = (double)C * (double)ev->n_events / (double)nW;
+  if (stage) return chunk_rows <= 1.5 * (kStreamWaves * 64 * kStreamEPT) * (double)T;
+  if (T > 256 && T <= 384) return chunk_rows <= 1.8e6;
+  return chunk_rows <= (cells && nW >= 1000 ? 1.15e6 : 1.0e6);
+}
+
+SegPlan seg_plan(const tre_events* ev, bool stage, bool cells) {
   SegPlan g;
   const int64_t T = ev->n_traces, M = ev->cfg.n_models, nW = ev->n_windows;
   const int64_t C = chunk_windows((int)M, ev->wcap);
-  if (T > (stage ? kSegStage : kSegTraces)) {
-    const double chunk_rows = (double)C * (double)ev->n_events / ((double)T * (double)nW);
-    const int64_t tile = (int64_t)(stage ? kStreamWaves : stream_waves((uint32_t)T)) * 64 * kStreamEPT;
-    if (T > kSegSparse || chunk_rows > 1.5 * (double)tile) return g;
-  }
+  if (!seg_pays(ev, stage, cells)) return g;
   const int64_t most = std::min<int64_t>({(int64_t)kSegMax, (kSegGrid + T - 1) / T, (nW + C - 1) / C});
   if (most < 2) return g;
   const int64_t per = (nW + most - 1) / most;
@@ -3211,7 +3232,8 @@ static int launch_segments(const tre_events* ev, const SegPlan& g, StreamParams 
 static int launch_stream(const tre_events* ev, const StreamParams& p, hipStream_t st, char* ws = nullptr,
                          size_t ws_bytes = 0) {
   const bool stage = p.stage64 || p.stage32 || p.sflags;
-  const SegPlan g = seg_plan(ev, stage);
+  const bool cells = p.prefill || p.decode || p.a_int || p.w_int || p.tss64 || p.tss32 || p.flags;
+  const SegPlan g = seg_plan(ev, stage, cells);
   if (g.nseg && ws) {
     if (g.bytes <= ws_bytes) return launch_segments(ev, g, p, stage, ws, st);
   } else if (g.nseg) {
@@ -3220,7 +3242,6 @@ static int launch_stream(const tre_events* ev, const StreamParams& p, hipStream_
   }
   const size_t lds = stream_lds(ev, stage);
   LaunchTimer lt("tss_stream", st);
-  const bool cells = p.prefill || p.decode || p.a_int || p.w_int || p.tss64 || p.tss32 || p.flags;
   const int waves = stream_waves(ev->n_traces);
   if (stage)
     hipLaunchKernelGGL((tss_stream_stage<kStreamWaves, kStreamEPT>), dim3(ev->n_traces),

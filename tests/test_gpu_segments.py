@@ -55,6 +55,16 @@ def test_edges(lib, M, n_windows, n_traces, window_ms, fast_w, slow_w):
     S._check(lib, w.name, w.trace_cfg(), traces, prof)
 
 
+# the numbers of chunks, windows and traces at which the path changes, and (161
+# and 400 traces) rows of a chunk on either side of the line
+@pytest.mark.parametrize("M,n_windows,n_traces,window_ms", [
+    (2, 96, 3, 500), (2, 97, 3, 500), (3, 64, 2, 500), (3, 65, 2, 500), (40, 39, 2, 200), (40, 40, 2, 200),
+    (16, 48, 2, 250), (16, 49, 2, 250), (5, 130, 160, 500), (5, 130, 161, 500), (17, 41, 96, 100), (17, 41, 97, 100),
+    (64, 44, 161, 500), (64, 44, 400, 1000)])
+def test_rule_edges(lib, M, n_windows, n_traces, window_ms):
+    test_edges(lib, M, n_windows, n_traces, window_ms, 4, 8)
+
+
 def test_stage_columns(lib):
     """8 and 9 models: 16 and 18 share columns."""
     for M in (8, 9):
