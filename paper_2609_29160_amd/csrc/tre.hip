@@ -1410,7 +1410,7 @@ struct SegNetParams {
   const uint8_t* type;
   const int64_t* off;
   int64_t window_ms;
-  int32_t n_windows, M, nseg, seg_w;
+  int32_t M, nseg, seg_w;
   int32_t* seg_row;             // [trace][nseg + 1]
   unsigned long long* seg_net;  // [trace][nseg][M]
   uint32_t* first;              // [trace][K], set to "none" here
@@ -3147,7 +3147,6 @@ static int launch_segments(const tre_events* ev, const SegPlan& g, StreamParams 
   np.type = p.type;
   np.off = p.off;
   np.window_ms = p.window_ms;
-  np.n_windows = p.n_windows;
   np.M = M;
   np.nseg = g.nseg;
   np.seg_w = g.seg_w;
@@ -3289,10 +3288,16 @@ static int act_windows(const tre_events* ev, const tre_actuation* act, ActWindow
   return TRE_OK;
 }
 
-// a workgroup of four waves per scenario while the chip holds them all at
-// once (1024 scenarios x 720 ticks x 8 models: 223 us against 526 us with one
-// wave each); above, the folds' fewer instructions count
-constexpr uint32_t kOrdScenarios = 2048;
+// Scenarios up to which each gets a workgroup of four waves (rebalance_ordered).
+// 1536 of them are on the chip at once (six a CU, by LDS and registers). Ordering
+// a tick costs an instruction stream per model, the folds hardly grow with the
+// models, so the line falls with them; measured, one wave a scenario / four, us
+// for 360 ticks: 8 models: 1024 scenarios 312 / 143, 1536 341 / 169, 2048 341 /
+// 276; under actuation 1536 413 / 255, 2048 414 / 429; 16 models: 2048 368 / 317;
+// 32 models: 768 398 / 317 (seldom moving 337 / 302), 1024 seldom moving 336 /
+// 361, 2048 433 / 658; 40 models: 256 405 / 360 (720 ticks 658 / 689), 512 408 /
+// 527; 64 models: 64 446 / 525, 2048 491 / 2359.
+static uint32_t ord_scenarios(int M, bool act) { return M <= 16 ? (act ? 1536 : 2048) : M <= 32 ? 768 : 0; }
 
 static int launch_rebalance(const tre_events* ev, const tre_profile* prof, const double* vals,
                             const uint8_t* flags, const tre_scenario* sc, uint32_t n_sc,
@@ -3326,9 +3331,10 @@ static int launch_rebalance(const tre_events* ev, const tre_profile* prof, const
   // one wave per scenario, four per workgroup
   const dim3 grid((unsigned)(((uint64_t)n_sc + 3) / 4)), block(256);
   LaunchTimer lt("rebalance", st);
-  if (n_sc <= kOrdScenarios && aw)
+  const bool ordered = n_sc <= ord_scenarios(c.M, aw != nullptr);
+  if (ordered && aw)
     hipLaunchKernelGGL(rebalance_ordered<true>, dim3(n_sc), dim3(64 * (kOrdWaves + 1)), 0, st, c);
-  else if (n_sc <= kOrdScenarios)
+  else if (ordered)
     hipLaunchKernelGGL(rebalance_ordered<false>, dim3(n_sc), dim3(64 * (kOrdWaves + 1)), 0, st, c);
   else if (aw)
     hipLaunchKernelGGL(rebalance<true>, grid, block, 0, st, c);

@@ -13,6 +13,7 @@ import numpy as np
 import pytest
 
 import parity as PT
+import test_gpu_actuation as A
 import test_gpu_parity as P
 import test_gpu_stage as S
 import tracegen as tg
@@ -80,6 +81,25 @@ def test_scenario_counts(lib, n_sc):
     evs = w.generate(0, 1)
     sc = P._random_scenarios(1, n_sc, 11)
     P._check_set(lib, f"{n_sc} scenarios", w.trace_cfg(), [evs.trace(0)], w.profile_columns(1), sc)
+
+
+@pytest.mark.parametrize("M,n_sc,act", [(16, 1536, True), (16, 1537, True), (17, 768, False), (17, 769, True), (32, 768, True),
+                                        (32, 3, False), (33, 1, False), (33, 3, True)])
+def test_replay_rule(lib, M, n_sc, act):
+    """The models and scenarios at which the replay changes kernels, every window
+    a tick."""
+    w = _workload(M, 50, 1, 500, M, 1, 2)
+    evs = w.generate(0, 1)
+    sc = P._random_scenarios(1, n_sc, 11)
+    if not act:
+        P._check_set(lib, f"{M} models {n_sc} scenarios", w.trace_cfg(), [evs.trace(0)], w.profile_columns(1), sc)
+        return
+    rng = np.random.default_rng(M)
+    g = rng.integers(1, 3, (1, M)).astype(np.int32)
+    cfg = dict(w.trace_cfg(), budget=int((g[0] * np.asarray(w.r_init)).sum()) + 3)
+    veto = rng.integers(0, 1 << 63, (1, 50), dtype=np.int64).astype(np.uint64) & np.uint64((1 << M) - 1)
+    veto[rng.random(veto.shape) > 0.2] = 0
+    A._check(lib, f"{M} models {n_sc} scenarios", cfg, [evs.trace(0)], w.profile_columns(1), sc, 1310, 1870, g, veto)
 
 
 def test_captured_sweep(lib):
