@@ -27,6 +27,16 @@
  *   - Per-cell arrays are laid out [trace][window][model], row-major.
  *   - Handles are immutable after tre_load_events; concurrent calls on one
  *     handle with distinct outputs and workspaces are safe.
+ *   - Device memory: the caller's, but for each handle's small tables and for
+ *     blocks that the library keeps per device, at most 1 GiB in all. They
+ *     serve tre_load_events with TRE_VALIDATE, and tre_eval_tss,
+ *     tre_eval_stage, tre_sweep and tre_sweep_act on few traces (8 bytes per
+ *     trace, window and model, 16 for the stage shares, and some per segment),
+ *     in stream order. Where there is no block to be had, and on a stream
+ *     under capture, those calls take a path without one, with the same
+ *     results. When a device's last handle is freed at most one block stays,
+ *     of up to twice what the largest call since the last such time needed
+ *     (none after a load that is refused). tre_sweep_noalloc takes none.
  *   - Floating point: IEEE binary64, round to nearest even, no contraction,
  *     in the operation order documented at tre_eval_tss; results are
  *     bit-identical across launches and grid shapes.
@@ -202,10 +212,12 @@ const char* tre_last_error(void);
    The first three are checked together and the message names the lowest
    failing row and its kind; TRE_ESTATE is checked only when they pass
    (the lowest failing row, or the smallest trace and id in error).
-   The id checks allocate temporary device memory: one bit per id up to the
-   largest admitted id of each trace, then 4 bytes and one bit per id up to
-   the largest ARRIVE or FINISH id (at most 256 MiB at a time, or one
-   trace's tables if larger), freed before the call returns. Without
+   The checks take temporary device memory: 8 bytes per piece of rows (2048
+   or more) and model, then, for the ids, one bit per id up to the largest
+   admitted id of each trace, and 4 bytes and one bit per id up to the
+   largest ARRIVE or FINISH id (bits rounded up to a power of two; at most
+   256 MiB of either at a time, or one trace's tables if larger). What does
+   not fit the library's blocks is freed before the call returns. Without
    TRE_VALIDATE, events that break these rules give unspecified results,
    never an access outside the columns, outputs or workspace. The
    handle owns small device tables (offsets, tick list); free it with
@@ -579,7 +591,11 @@ int tre_loop_act(const tre_trace_cfg* cfg, uint32_t n_traces, const tre_loop_req
    "calib_fill", "calib_stream", "calib_fallback" (the second stream tier
    and the chunked path together), "calib_fit", "calib_order",
    "loop_replay", "stage_tss")
-   and returns their total milliseconds and count, then forgets them. */
+   and returns their total milliseconds and count, then forgets them.
+   "tss_stream" is every form of the pass over the events (with few traces three
+   kernels, counted as one launch, the control replay of a trace with one
+   scenario among them), "loop_replay" every form of the closed loop,
+   "validate" the first of the load checks. */
 int tre_set_timing(int enable);
 int tre_kernel_time(const char* kernel, double* total_ms, uint64_t* launches);
 

@@ -2484,48 +2484,135 @@ __global__ __launch_bounds__(256) void id_scan(IdParams p) {
 }
 
 // ------------------------------------------------ scratch of one call
-// The segmented path's scratch comes from a memory pool of the library's own
-// per device, allocated and freed in stream order, so that calls on several
-// streams or threads never share it. The pool keeps up to kPoolKeep bytes
-// between calls and gives everything back when the device's last handle is
-// freed. A stream that is being captured gets none (the caller then takes
-// the path that needs no scratch).
-constexpr uint64_t kPoolKeep = 512ull << 20;
+// The segmented path's scratch and the load checks' memory come from blocks that
+// the library keeps per device. A block serves one call at a time, from the
+// constructor to the destructor on the host and from there to the block's event
+// on the device: another call takes it once the event has completed, or on the
+// same stream behind it. So calls on several streams and threads never share
+// one. (A HIP memory pool gives its memory back at every hipMalloc and hipFree of
+// the process, whatever its release threshold: the first call on new traces
+// mapped its scratch anew, 350 to 500 us.)
+//
+// The blocks of a device hold at most kPoolKeep in all, and no call takes more.
+// When the device's last handle is freed one block of once to twice what the
+// largest call since the last such time needed is kept for the next handle's
+// calls, and the others are given back; all of them after a load that is refused.
+// A stream that is being captured gets none (the caller then takes the path that
+// needs no scratch).
+constexpr uint64_t kPoolKeep = 1ull << 30;
+constexpr int kPoolBlocks = 16;
 
 namespace {
 constexpr int kMaxDevices = 256;
+struct Block {
+  void* ptr;
+  uint64_t bytes;
+  hipEvent_t done;  // recorded behind the last call's work
+  hipStream_t st;   // its stream
+  bool busy;        // a call holds it
+};
+struct Pool {
+  int handles;
+  uint64_t need;   // largest call since the device last had no handle
+  uint64_t bytes;  // of all blocks
+  Block b[kPoolBlocks];
+};
 std::mutex g_pool_mu;
-hipMemPool_t g_pool[kMaxDevices];
-bool g_pool_tried[kMaxDevices];
-int g_handles[kMaxDevices];
+Pool g_pool[kMaxDevices];
 
-hipMemPool_t pool_for(int dev) {
-  if (dev < 0 || dev >= kMaxDevices) return nullptr;
-  std::lock_guard<std::mutex> lk(g_pool_mu);
-  if (!g_pool_tried[dev]) {
-    g_pool_tried[dev] = true;
-    hipMemPoolProps props{};
-    props.allocType = hipMemAllocationTypePinned;
-    props.location.type = hipMemLocationTypeDevice;
-    props.location.id = dev;
-    uint64_t keep = kPoolKeep;
-    hipMemPool_t pool = nullptr;
-    if (hipMemPoolCreate(&pool, &props) == hipSuccess &&
-        hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) == hipSuccess)
-      g_pool[dev] = pool;
-    (void)hipGetLastError();
-  }
-  return g_pool[dev];
+bool block_done(const Block& b) {
+  const hipError_t e = hipEventQuery(b.done);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e == hipSuccess;
 }
 
-void count_handle(int dev, int d) {
+void block_free(Pool& p, Block& b) {
+  (void)hipEventSynchronize(b.done);
+  (void)hipEventDestroy(b.done);
+  (void)hipFree(b.ptr);
+  p.bytes -= b.bytes;
+  b = Block{};
+}
+
+// A block of at least `bytes` for work on `st`, marked busy, or NULL. The smallest
+// that fits among those free to use, else a new one, for which blocks free to
+// use are given back (waiting for the device) while all of them would hold more
+// than kPoolKeep.
+Block* block_take(int dev, uint64_t bytes, hipStream_t st) {
+  if (dev < 0 || dev >= kMaxDevices || bytes > kPoolKeep) return nullptr;
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  Pool& p = g_pool[dev];
+  p.need = std::max(p.need, bytes);
+  Block *fit = nullptr, *slot = nullptr;
+  for (Block& b : p.b) {
+    if (!b.ptr) slot = &b;
+    else if (!b.busy && b.bytes >= bytes && (!fit || b.bytes < fit->bytes) && (b.st == st || block_done(b))) fit = &b;
+  }
+  if (fit) {
+    // (the stream that had this handle may be gone and its work still under way)
+    if (fit->st == st && hipStreamWaitEvent(st, fit->done, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    fit->busy = true;
+    return fit;
+  }
+  // nothing below is part of a capture that goes on elsewhere
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  for (Block& b : p.b) {
+    if (slot && p.bytes + bytes <= kPoolKeep) break;
+    if (b.ptr && !b.busy && block_done(b)) {
+      block_free(p, b);
+      slot = &b;
+    }
+  }
+  Block nb{};
+  nb.bytes = bytes;
+  nb.busy = true;
+  const bool room = slot && p.bytes + bytes <= kPoolKeep;
+  if (room && hipMalloc(&nb.ptr, bytes) != hipSuccess) nb.ptr = nullptr;
+  if (nb.ptr && hipEventCreateWithFlags(&nb.done, hipEventDisableTiming) != hipSuccess) {
+    (void)hipFree(nb.ptr);
+    nb.ptr = nullptr;
+  }
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!nb.ptr) {
+    if (room) (void)hipGetLastError();
+    return nullptr;
+  }
+  p.bytes += bytes;
+  *slot = nb;
+  return slot;
+}
+
+// the call's work is enqueued on `st`
+void block_return(Block* b, hipStream_t st) {
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  if (hipEventRecord(b->done, st) != hipSuccess) {  // then the event's last record stands: wait instead
+    (void)hipGetLastError();
+    (void)hipStreamSynchronize(st);
+  }
+  b->st = st;
+  b->busy = false;
+}
+
+void count_handle(int dev, int d, bool refused = false) {
   if (dev < 0 || dev >= kMaxDevices) return;
   std::lock_guard<std::mutex> lk(g_pool_mu);
-  g_handles[dev] += d;
-  if (g_handles[dev] == 0 && g_pool[dev]) (void)hipMemPoolTrimTo(g_pool[dev], 0);
+  Pool& p = g_pool[dev];
+  p.handles += d;
+  if (p.handles > 0) return;
+  Block* keep = nullptr;
+  if (!refused)
+    for (Block& b : p.b)
+      if (b.ptr && b.bytes >= p.need && b.bytes <= 2 * p.need && (!keep || b.bytes < keep->bytes)) keep = &b;
+  for (Block& b : p.b)
+    if (b.ptr && !b.busy && &b != keep) block_free(p, b);
+  p.need = 0;
 }
 
-// `bytes` of scratch for work enqueued on `st`, or NULL
+// `bytes` of scratch for work enqueued on `st` until the destructor, or NULL
 class Scratch {
  public:
   Scratch(int dev, size_t bytes, hipStream_t st) : st_(st) {
@@ -2534,22 +2621,18 @@ class Scratch {
       (void)hipGetLastError();
       return;
     }
-    hipMemPool_t pool = pool_for(dev);
-    if (!pool) return;
-    if (hipMallocFromPoolAsync(&ptr_, bytes, pool, st) != hipSuccess) {
-      ptr_ = nullptr;
-      (void)hipGetLastError();
-    }
+    b_ = block_take(dev, (bytes + kRound - 1) & ~(kRound - 1), st);
   }
   ~Scratch() {
-    if (ptr_) (void)hipFreeAsync(ptr_, st_);
+    if (b_) block_return(b_, st_);
   }
   Scratch(const Scratch&) = delete;
   Scratch& operator=(const Scratch&) = delete;
-  char* get() const { return (char*)ptr_; }
+  char* get() const { return b_ ? (char*)b_->ptr : nullptr; }
 
  private:
-  void* ptr_ = nullptr;
+  static constexpr uint64_t kRound = 1ull << 20;  // calls of nearly one size share a block
+  Block* b_ = nullptr;
   hipStream_t st_;
 };
 
@@ -2670,7 +2753,6 @@ static int stream_waves(uint32_t n_traces) {
 // before its own), each a whole number of evaluation chunks; workgroups of 16
 // waves while they are at most kSegWide. It costs three launches, 2 bytes a row
 // and 16 bytes a cell more than one workgroup per trace (seg_pays).
-constexpr size_t kSegScratchMax = 1ull << 30;
 constexpr int64_t kSegGrid = 2048, kSegMax = 256, kSegWide = 512;
 
 static size_t stream_lds(const tre_events* ev, bool stage = false) {
@@ -2684,7 +2766,7 @@ static size_t stream_lds(const tre_events* ev, bool stage = false) {
   return ring + 3 * C * M * 8 + M * sizeof(CtlModel) + ((11 * 4 + 7) & ~(size_t)7);
 }
 
-// Device memory of one call: from the pool, or its own when the pool gives none
+// Device memory of one call: a kept block, or its own when there is none to be had
 class CallMemory {
  public:
   CallMemory(int dev, size_t bytes, hipStream_t st) : pooled_(dev, bytes, st) {
@@ -2863,6 +2945,12 @@ static int validate_events(const tre_events* ev, hipStream_t st) {
   return TRE_OK;
 }
 
+static void free_events(tre_events* ev, bool refused) {
+  if (ev->d_off) (void)hipFree(ev->d_off);  // with the tick tables
+  if (ev->counted) count_handle(ev->device, -1, refused);
+  delete ev;
+}
+
 extern "C" int tre_load_events(const int64_t* ts, const uint8_t* model, const uint32_t* req,
                                const uint8_t* type, const uint16_t* tokens,
                                const int64_t* trace_off, uint32_t n_traces,
@@ -2924,10 +3012,12 @@ extern "C" int tre_load_events(const int64_t* ts, const uint8_t* model, const ui
   hipStream_t st = (hipStream_t)stream;
   int rc = TRE_OK;
   auto cleanup = [&](int code) {
-    tre_free_events(ev);
+    free_events(ev, true);
     return code;
   };
   if (hipGetDevice(&ev->device) != hipSuccess) return cleanup(fail(TRE_EHIP, "hipGetDevice failed"));
+  count_handle(ev->device, 1);
+  ev->counted = true;
   // the handle's tables in one allocation and one copy: offsets, tick windows, tick kinds
   const size_t off_bytes = sizeof(int64_t) * ((size_t)n_traces + 1), tw_bytes = sizeof(uint32_t) * (tw.size() + 1);
   std::vector<char> tables(off_bytes + tw_bytes + tk.size() + 1);
@@ -2946,17 +3036,12 @@ extern "C" int tre_load_events(const int64_t* ts, const uint8_t* model, const ui
     rc = validate_events(ev, st);
     if (rc != TRE_OK) return cleanup(rc);
   }
-  count_handle(ev->device, 1);
-  ev->counted = true;
   *out = ev;
   return TRE_OK;
 }
 
 extern "C" void tre_free_events(tre_events* ev) {
-  if (!ev) return;
-  if (ev->counted) count_handle(ev->device, -1);
-  if (ev->d_off) (void)hipFree(ev->d_off);  // with the tick tables
-  delete ev;
+  if (ev) free_events(ev, false);
 }
 
 extern "C" int tre_events_info(const tre_events* ev, tre_info* info) {
@@ -3130,7 +3215,7 @@ SegPlan seg_plan(const tre_events* ev, bool stage, bool cells) {
   g.net = take((size_t)T * nseg * M * sizeof(unsigned long long));
   g.row = take((size_t)T * (nseg + 1) * sizeof(int32_t));
   g.first = take((size_t)T * g.K * sizeof(uint32_t));
-  if (g.bytes > kSegScratchMax) return g;
+  if (g.bytes > kPoolKeep) return g;
   g.nseg = (int32_t)nseg;  // > 0: the path applies
   return g;
 }
@@ -3227,7 +3312,7 @@ static int launch_segments(const tre_events* ev, const SegPlan& g, StreamParams 
 }
 
 // ws, ws_bytes: scratch the caller holds for the segmented path; without it
-// the call takes its own from the pool
+// the call takes a kept block
 static int launch_stream(const tre_events* ev, const StreamParams& p, hipStream_t st, char* ws = nullptr,
                          size_t ws_bytes = 0) {
   const bool stage = p.stage64 || p.stage32 || p.sflags;

@@ -6,8 +6,9 @@ wrong: columns at the edges of the chain's two forms (16 and 17 models, 8 and
 segment, fewer windows than a chunk, every window a tick, more moves per tick
 than models, and the number of scenarios at which the replay changes kernels.
 Every per-cell output, decision and replica sum equals the oracle's bit for
-bit. A sweep captured in a graph takes no scratch of the library's pool; its
-replays equal the eager call."""
+bit. A sweep captured in a graph takes no scratch of the library's own; its
+replays equal the eager call. The scratch is kept and given back within its
+bounds and shared by no two calls of several threads and streams."""
 import edge_traces as E
 import numpy as np
 import pytest
@@ -211,3 +212,127 @@ def _eval(tre, ev, prof):
     out = tre.tss_outputs(ev, which=("tss64", "flags"))
     tre.tre_eval_tss(ev, prof, out)
     return out
+
+
+def test_beside_a_capture(lib):
+    """A call on a stream of its own while another stream is being captured: the
+    capture goes on, and the call's outputs and the graph's are right."""
+    tre, device, torch = lib
+    w = _workload(8, 200, 4, 250, 21, 4, 8)
+    dt = device.upload(w)
+    ev = device.load(dt)
+    prof = device.profiles(w)
+    ref = {k: v.clone() for k, v in _eval(tre, ev, prof).items()}
+    got, other = tre.tss_outputs(ev, which=("tss64", "flags")), tre.tss_outputs(ev, which=("tss64", "flags"))
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    x = torch.zeros(1024, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=a):
+        x.add_(1.0)
+        tre.tre_eval_tss(ev, prof, got, stream=b)
+        tre.tre_eval_tss(ev, prof, other)
+        x.add_(1.0)
+    torch.cuda.synchronize()
+    for k in ref:
+        assert torch.equal(got[k].view(torch.uint8), ref[k].view(torch.uint8)), k
+    x.zero_()
+    g.replay()
+    torch.cuda.synchronize()
+    assert float(x.min()) == 2.0 == float(x.max())
+    for k in ref:
+        assert torch.equal(other[k].view(torch.uint8), ref[k].view(torch.uint8)), k
+    ev.close()
+
+
+def _held(torch):
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free, total = torch.cuda.mem_get_info()
+    return total - free
+
+
+def test_scratch_is_given_back(lib):
+    """Scratch of 384 MiB (150 traces x 24 models x 14000 windows, empty): kept past
+    the last handle, while the next handles need as much; given back once they
+    need less, and by a load that is refused. A call that would need more than
+    1 GiB takes none."""
+    tre, device, torch = lib
+    T, M, nW, big = 150, 24, 14_000, 300 << 20
+    cols = {k: torch.zeros(16, dtype=d, device="cuda") for k, d in
+            (("ts", torch.int64), ("model", torch.uint8), ("req", torch.uint32), ("type", torch.uint8), ("tokens", torch.uint16))}
+    w = _workload(M, nW, T, 100, 1, 50, 100)
+    prof = tre.pack(w.profile_columns(T), tre.PROFILE_DTYPE)
+
+    def load(off, cfg, **kw):
+        return tre.tre_load_events(cols["ts"], cols["model"], cols["req"], cols["type"], cols["tokens"], off, cfg, **kw)
+
+    def turn(n_traces, n_windows):
+        ev = load(np.zeros(n_traces + 1, np.int64), dict(w.trace_cfg(), duration_ms=100 * n_windows))
+        t32 = tre.tss_outputs(ev, which=("flags",))
+        tre.tre_eval_tss(ev, prof, t32)
+        torch.cuda.synchronize()
+        assert int(t32["flags"].min()) == 1 == int(t32["flags"].max())  # idle, never initialised
+        ev.close()
+    turn(1, 1000)
+    before = _held(torch)
+    turn(T, nW)
+    assert _held(torch) > before + big
+    turn(T, nW)
+    assert _held(torch) > before + big
+    turn(1, 1000)
+    assert _held(torch) < before + (16 << 20)
+    turn(T, 38_000)
+    assert _held(torch) < before + (16 << 20)
+    turn(T, nW)
+    # a load refused at its last check, after tables of 4 bytes for each of 2^27 ids
+    cols["ts"].copy_(torch.arange(16))
+    cols["req"].copy_(torch.full((16,), 1 << 27, dtype=torch.int64))  # sixteen ARRIVE rows of one id
+    with pytest.raises(tre.TreError) as e:
+        load(np.array([0, 16]), w.trace_cfg())
+    assert e.value.code == tre.TRE_ESTATE
+    assert _held(torch) < before + (16 << 20)
+
+
+def test_streams_and_threads(lib):
+    """Calls of several threads on streams of their own, at once, on trace sets of
+    their own: each one's outputs are those of the same call alone."""
+    import threading
+    tre, device, torch = lib
+    sets, errors = [], []
+    for i, (M, nW, T) in enumerate([(8, 700, 5), (20, 400, 9), (3, 1500, 3), (16, 900, 2)]):
+        w = _workload(M, nW, T, 250, 40 + i, 4, 8)
+        ev, prof = device.load(device.upload(w)), device.profiles(w)
+        ref = {k: v.clone() for k, v in tre.tss_outputs(ev).items()}
+        tre.tre_eval_tss(ev, prof, ref)
+        st = tre.stage_outputs(ev)
+        tre.tre_eval_stage(ev, prof, st)
+        sets.append((ev, prof, ref, st))
+    torch.cuda.synchronize()
+
+    def work(ev, prof, ref, sref):
+        try:
+            stream = torch.cuda.Stream()
+            for _ in range(12):
+                with torch.cuda.stream(stream):
+                    outs = [tre.tss_outputs(ev) for _ in range(3)]
+                    st = tre.stage_outputs(ev)
+                    for o in outs:
+                        tre.tre_eval_tss(ev, prof, o)
+                    tre.tre_eval_stage(ev, prof, st)
+                stream.synchronize()
+                for o in outs:
+                    for k in ref:
+                        assert torch.equal(o[k].view(torch.uint8), ref[k].view(torch.uint8)), k
+                for k in sref:
+                    assert torch.equal(st[k].view(torch.uint8), sref[k].view(torch.uint8)), k
+        except Exception as e:  # noqa: BLE001 (reported below)
+            errors.append(e)
+    threads = [threading.Thread(target=work, args=s) for s in sets]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert not errors, errors
+    for s in sets:
+        s[0].close()
