@@ -2262,8 +2262,9 @@ __global__ __launch_bounds__(256) void net_scan(unsigned long long* net, const u
 // model m that is the count after its last row with that timestamp.
 //
 // One wave per piece of a trace, 64 rows per step, one per lane, from the
-// counts before the piece (net_scan); on rows that fail the other checks the
-// result is not read. Rows of the same model are found with ballots over the
+// counts before the piece (net_scan); it does nothing where rows failed the other
+// checks (an instant could then be a whole trace, and every piece would read on
+// to its end). Rows of the same model are found with ballots over the
 // model's bits; a lane's count is its model's carry plus the signed
 // transitions of the same-model lanes up to it. A row whose next same-model
 // row in the step has a later timestamp is the last of its instant and is
@@ -2297,6 +2298,7 @@ __global__ __launch_bounds__(256) void validate_state(StateParams p) {
   int* const cw = s_w[wv];
   uint32_t* const lt = s_t[wv];
   int* const lr = s_r[wv];
+  if (*p.err & ((1u << kValState) - 1u)) return;  // the whole grid: those bits are set before this kernel
   const int nbits = p.M > 1 ? 32 - __clz(p.M - 1) : 0;
   const unsigned long long le = (2ull << lane) - 1ull;  // lanes <= this one
   auto fence = [] {
@@ -2369,7 +2371,9 @@ __global__ __launch_bounds__(256) void validate_state(StateParams p) {
       fence();
     }
     // each model's last row is the last of its instant unless a later piece
-    // goes on with it: rows after this piece at the timestamp of its last row
+    // goes on with it: rows after this piece at the timestamp of its last row,
+    // read until every such model has been seen again (an instant has at most
+    // 65535 rows, the limit of its window)
     const bool neg = lane < p.M && lr[lane] >= 0 && (ca[lane] < 0 || cw[lane] < 0);
     bool on = false;
     const uint32_t tl = (uint32_t)ts_[r_end - 1];
@@ -2385,7 +2389,7 @@ __global__ __launch_bounds__(256) void validate_state(StateParams p) {
           on = on || __builtin_amdgcn_readlane(m, l) == lane;
           rows &= rows - 1ull;
         }
-        if (!more) break;
+        if (!more || !__ballot(neg && lt[lane] == tl && !on)) break;
       }
     }
     if (neg && !(lt[lane] == tl && on)) bad = bad < lr[lane] ? bad : lr[lane];

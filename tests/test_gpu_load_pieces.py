@@ -2,8 +2,10 @@
 wave each): counts that go negative in, at the edge of and after a piece, an
 instant that spans the edge with the model's rows on both sides, and an
 instant longer than a piece. The row in the message equals the lowest last
-row of an instant with a negative count, from a cumulative sum on the host."""
+row of an instant with a negative count, from a cumulative sum on the host. A
+trace that is one instant is refused for its range, in the time of a load."""
 import re
+import time
 
 import edge_traces as E
 import numpy as np
@@ -85,3 +87,31 @@ def test_pieces(lib, lead, kind):
         assert e.value.code == tre.TRE_ESTATE
         got = re.match(r".*row (\d+): an active", str(e.value))
         assert got and int(got[1]) == int(off[1]) + row, (str(e.value), int(off[1]) + row)
+
+
+def test_one_instant(lib):
+    """2^23 rows of one timestamp, FINISH rows first: too many for their window, and
+    every piece's counts are negative to the last row. Refused without reading each
+    piece's instant to its end."""
+    tre, device, torch = lib
+    n = 1 << 23
+    ts = np.arange(n) * 20_000 // n
+    ty = np.array([ARR, ADM, DEC, FIN], np.uint8)[np.arange(n) % 4]
+    bad = {"ts": np.full(n, 5), "model": np.zeros(n), "req": np.zeros(n), "tokens": np.ones(n),
+           "type": np.where(np.arange(n) < n // 3, FIN, np.where(np.arange(n) < 2 * n // 3, ADM, ARR))}
+    good = dict(bad, ts=ts, type=ty, model=np.arange(n) // 4 % M)
+    best = {}
+    for name, tr in (("good", good), ("bad", bad)):
+        cols, off = _columns_from_host(torch, [{k: np.asarray(v).astype(d) for k, v, d in
+                                               ((k, tr[k], d) for k, d in (("ts", np.int64), ("model", np.uint8), ("req", np.uint32),
+                                                                           ("type", np.uint8), ("tokens", np.uint16)))}])
+        for _ in range(3):
+            t0 = time.perf_counter()
+            try:  # windows of 1 ms: 419 rows each
+                tre.tre_load_events(cols["ts"], cols["model"], None, cols["type"], cols["tokens"], off,
+                                    _cfg(M, 1, 20_000, fast_w=2, slow_w=4)).close()
+                assert name == "good"
+            except tre.TreError as e:
+                assert name == "bad" and e.code == tre.TRE_ERANGE and "row 0:" in str(e), (name, str(e))
+            best[name] = min(best.get(name, 1e9), time.perf_counter() - t0)
+    assert best["bad"] < 10 * best["good"] + 0.02, best
