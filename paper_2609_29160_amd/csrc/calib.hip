@@ -659,19 +659,35 @@ struct FallbackParams {
   uint32_t magic_w;             // as StreamParams
 };
 
+// The workgroups of a launch over the listed traces, as many to each as there are
+// for all (the list is known on the device only): a trace's are numbered
+// [0, per), and a group of them goes on to the trace `groups` further. One listed
+// trace gets them all.
+struct Share {
+  uint32_t n_list, per, groups, pos;
+  uint64_t first, stride;  // this thread's first item of a trace, and its step
+};
+__device__ __forceinline__ Share share_of(const uint32_t* fb) {
+  Share s;
+  s.n_list = fb[0];
+  s.per = s.n_list > 0 && s.n_list < gridDim.x ? gridDim.x / s.n_list : 1u;
+  s.groups = gridDim.x / s.per;  // at least n_list, or every workgroup
+  s.pos = blockIdx.x / s.per;
+  s.first = (uint64_t)(blockIdx.x % s.per) * 256 + threadIdx.x;
+  s.stride = (uint64_t)s.per * 256;
+  return s;
+}
+
 __global__ __launch_bounds__(256) void fb_reset(FallbackParams p) {
-  const uint32_t n_list = p.fb[0];
+  const Share s = share_of(p.fb);
   const uint64_t cw = (uint64_t)p.M * p.n_windows, tw = (uint64_t)p.req_cap * 4;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint32_t pos = blockIdx.y; pos < n_list; pos += gridDim.y) {
+  for (uint32_t pos = s.pos; pos < s.n_list; pos += s.groups) {
     const uint32_t t = p.fb[1 + pos];
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cw; i += stride)
-      p.counts[(uint64_t)t * cw + i] = 0u;
+    for (uint64_t i = s.first; i < cw; i += s.stride) p.counts[(uint64_t)t * cw + i] = 0u;
     if (p.tab)
-      for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < tw; i += stride)
-        p.tab[(uint64_t)t * tw + i] = kNone;
+      for (uint64_t i = s.first; i < tw; i += s.stride) p.tab[(uint64_t)t * tw + i] = kNone;
     if (p.reqs) {
-      for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < p.req_cap; i += stride) {
+      for (uint64_t i = s.first; i < p.req_cap; i += s.stride) {
         unsigned long long* w = (unsigned long long*)(p.reqs + (uint64_t)t * p.req_cap + i);
         w[0] = 0ull;
         w[1] = 0ull;
@@ -797,9 +813,10 @@ __global__ __launch_bounds__(kJoinThreads) void calib_join(FallbackParams p) {
 
 // One thread per (listed trace, request slot).
 __global__ __launch_bounds__(256) void calib_judge(FallbackParams p) {
-  const uint32_t n_list = p.fb[0], win = (uint32_t)p.window_ms;
-  for (uint32_t pos = blockIdx.y; pos < n_list; pos += gridDim.y)
-    for (uint64_t r = (uint64_t)blockIdx.x * 256 + threadIdx.x; r < p.req_cap; r += (uint64_t)gridDim.x * 256) {
+  const Share s = share_of(p.fb);
+  const uint32_t win = (uint32_t)p.window_ms;
+  for (uint32_t pos = s.pos; pos < s.n_list; pos += s.groups)
+    for (uint64_t r = s.first; r < p.req_cap; r += s.stride) {
       const uint32_t t = p.fb[1 + pos];
       const uint64_t slot = (uint64_t)t * p.req_cap + r;
       const uint4 rec = ((const uint4*)p.tab)[slot];
@@ -1675,12 +1692,12 @@ extern "C" int tre_calibrate(const tre_events* ev, const tre_slo* slo, const dou
       f1.fb = l1;
       StreamParams sp{ev->ts, ev->model, ev->req, ev->type, ev->tokens, ev->d_off, slo, counts, reqs, bad,
                       l1, l2, req_cap, M, ev->cfg.window_ms, nW, window_magic(ev->cfg.window_ms)};
-      hipLaunchKernelGGL(fb_reset, dim3(64, 16), dim3(256), 0, st, f1);
+      hipLaunchKernelGGL(fb_reset, dim3(1024), dim3(256), 0, st, f1);
       hipLaunchKernelGGL((calib_stream<kBuckets2, kThreads2, kRows2>), dim3(ev->n_traces), dim3(kThreads2), 0, st, sp);
     }
-    hipLaunchKernelGGL(fb_reset, dim3(64, 16), dim3(256), 0, st, f2);
+    hipLaunchKernelGGL(fb_reset, dim3(1024), dim3(256), 0, st, f2);
     hipLaunchKernelGGL(calib_join, dim3(1024), dim3(kJoinThreads), 0, st, f2);
-    hipLaunchKernelGGL(calib_judge, dim3(128, 16), dim3(256), 0, st, f2);
+    hipLaunchKernelGGL(calib_judge, dim3(2048), dim3(256), 0, st, f2);
     lt.done();
     HIP_TRY(hipGetLastError());
   }

@@ -1,7 +1,8 @@
 """Calibration of few long traces, taken by request-id records at once: at the
 row count where the rule changes, with shorter and empty traces beside the
 long one, ids past req_cap, and req_cap one more than the longest trace's rows
-(then streamed). Every output equals the oracle's bit for bit."""
+(then streamed). Traces that the stream hands over take the same kernels. Every
+output equals the oracle's bit for bit."""
 import numpy as np
 import pytest
 import tracegen as tg
@@ -41,3 +42,20 @@ def test_records(lib, n_rows, cap, tiers):
     req_cap = most if cap is None else most + cap if cap < 0 else cap
     C._check(lib, f"records {n_rows} rows, req_cap {req_cap}", w.trace_cfg(), traces, w.profile_columns(3),
              w.slo_columns(3), req_cap, tiers=tiers)
+
+
+@pytest.mark.parametrize("n_listed", [1, 2, 700, 2050])
+def test_listed_traces(lib, n_listed):
+    """Traces that overflow both stream tiers, one to more than there are workgroups
+    (2048): their records are reset and judged by all of them together."""
+    over, fits = C._long_instant(4), C._turnover(400, 50)
+    traces = [fits] + [over] * n_listed + [fits]
+    n = len(traces)
+    C._check(lib, f"{n_listed} listed", C._small_cfg(2), traces, C._small_prof(2, n), C._small_slo(2, n), C._req_cap([over, fits]),
+             tiers=(n_listed, n_listed))
+
+
+def test_one_trace_by_records(lib):
+    w, traces = _traces(ROWS, 5)
+    C._check(lib, "one trace", w.trace_cfg(), traces[:1], w.profile_columns(1), w.slo_columns(1), C._req_cap(traces[:1]),
+             tiers=(0, 1))
