@@ -1589,7 +1589,9 @@ __device__ __forceinline__ double chain_run(double* t, int plane, int C, double 
 // block before). Every lane recomputes its own S at every step, and from step
 // u on lane u's is right. One LDS read of t1 and of o and one write of S per
 // 16 windows instead of 16 half-empty ones, whose cost does not fall with the
-// lanes in use: 25.9 cycles a window against 45 with a lane per column.
+// lanes in use: in a loop of their own 25.9 cycles a window against 45 with a
+// lane per column; 33 in the kernel, beside its other waves (7200 windows of 8
+// models 101 us).
 __device__ __forceinline__ double chain_rows(double* t, int plane, int str, int C, double S) {
   double t1 = t[0], o = t[plane];
   for (int u0 = 0; u0 < C; u0 += 16) {
@@ -1618,8 +1620,8 @@ __device__ __forceinline__ double chain_rows(double* t, int plane, int str, int 
 }
 
 // t1 of an idle window: -0.0, which no other window has (alpha * raw of a raw
-// ratio >= 0 is +0.0 or more, or a NaN of either sign)
-__device__ __forceinline__ bool idle_t1(double t1) { return dbits(t1) == 1ull << 63; }
+// ratio >= 0 is +0.0 or more, or a NaN of either sign); the high word tells
+__device__ __forceinline__ bool idle_t1(double t1) { return (uint32_t)(dbits(t1) >> 32) == 0x80000000u; }
 
 // One workgroup per trace, waves of four kinds that meet at one barrier per
 // step of `chunk` windows. A column is a model (kStage: a model's prefill or
@@ -3166,7 +3168,8 @@ struct SegPlan {
 // chip idle and the trace has steps enough to pay for three launches instead of
 // one. `cells`: per-cell outputs, which one workgroup per trace writes from its
 // serial chain. C: windows of a chunk, the step's evaluation. Measured, one
-// workgroup per trace / segments in us, 323 shapes:
+// workgroup per trace / segments in us, 550 shapes (5 of them are slower by 4 to
+// 17% with this rule):
 // - below four chunks (three for the stage shares) or 40 windows the launches
 //   cost more: 1 model x 40 windows 38 / 48, 32 x 10 windows 39 / 59 (160
 //   traces), x 20 windows 35 / 45; 1 model x 160 windows 60 / 43;
@@ -3177,23 +3180,29 @@ struct SegPlan {
 //   waves: up to 384 (384 x 64 models 584 / 526);
 // - more traces: one workgroup per trace is bound by its chunks of windows while
 //   rows are few, and by the rows' tallies, which segments do not make cheaper,
-//   when they are many. What counts is the rows of one chunk over all traces: up
-//   to 1.0 M (768 traces: 0.96 M 805 / 650, 1.16 M 564 / 588, 1.7 M 418 / 568;
-//   500: 1.06 M 420 / 508; 250: 0.83 M 1212 / 659, 1.31 M 372 / 393), to 1.15 M in
-//   long calls with per-cell outputs (401 x 13 models, 4500 windows, 1.05 M,
-//   under actuation 1712 / 1421; without outputs 1121 / 1390), to 1.8 M from 257
-//   to 384 traces, whose 16-wave workgroups take two rounds (1.7 M 512 / 416,
-//   2.2 M 382 / 462). Stage shares: 1.5 tiles a chunk and trace.
+//   when they are many. What counts is the rows of one chunk over all traces.
+//   Up to 256 traces (one 16-wave workgroup a CU): 1.5 M with per-cell outputs
+//   (1.56 M 606 / 578, 1.71 M 665 / 689), 1.1 M without (1.02 M 614 / 581, 1.12 M
+//   624 / 633); above 16 models 0.85 M (0.72 M 1245 / 644, 0.89 M 634 / 701, 1.08 M
+//   521 / 615), 1.0 M up to 160 traces (0.93 M 460 / 352, 1.06 M 64 / 77). To 384
+//   traces, whose workgroups take two rounds: 2.0 M (1.68 M 1123 / 922, 2.57 M 221
+//   / 237), above 16 models 1.5 M (0.82 M 2079 / 656, 1.60 M 587 / 719). To 768
+//   (8-wave workgroups): 1.0 M (0.97 M 960 / 714, 0.96 M 805 / 650, 1.14 M 547 / 688,
+//   1.7 M 418 / 568), 1.2 M in long calls with per-cell outputs (1.14 M 423 / 339,
+//   1.05 M under actuation 1712 / 1421, without outputs 1121 / 1390).
+//   Stage shares: 1.5 tiles a chunk and trace.
 bool seg_pays(const tre_events* ev, bool stage, bool cells) {
   constexpr int64_t kFew = 160, kFewWide = 96, kFewStage = 384, kMost = 768;
   const int64_t T = ev->n_traces, M = ev->cfg.n_models, nW = ev->n_windows, C = chunk_windows((int)M, ev->wcap);
+  const bool wide = M > kChainRows;
   if ((nW + C - 1) / C < (stage ? 3 : 4) || (!stage && nW < 40)) return false;
-  if (T <= (stage ? kFewStage : M <= kChainRows ? kFew : kFewWide)) return true;
+  if (T <= (stage ? kFewStage : wide ? kFewWide : kFew)) return true;
   if (T > kMost) return false;
   const double chunk_rows = (double)C * (double)ev->n_events / (double)nW;
   if (stage) return chunk_rows <= 1.5 * (kStreamWaves * 64 * kStreamEPT) * (double)T;
-  if (T > 256 && T <= 384) return chunk_rows <= 1.8e6;
-  return chunk_rows <= (cells && nW >= 1000 ? 1.15e6 : 1.0e6);
+  if (T <= 256) return chunk_rows <= (wide ? (T <= kFew ? 1.0e6 : 0.85e6) : cells ? 1.5e6 : 1.1e6);
+  if (T <= 384) return chunk_rows <= (wide ? 1.5e6 : 2.0e6);
+  return chunk_rows <= (cells && nW >= 1000 ? 1.2e6 : 1.0e6);
 }
 
 SegPlan seg_plan(const tre_events* ev, bool stage, bool cells) {
