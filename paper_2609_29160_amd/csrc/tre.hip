@@ -1986,14 +1986,12 @@ __global__ __launch_bounds__(256) void rebalance(CtlParams p) {
   if (lane == 0) p.n_moves[s] = st.nm;
 }
 
-// The same replay with one workgroup per scenario: three waves prepare the
-// ticks of the next batch (tick_order) while the fourth decides those of the
-// one before it.
-constexpr int kOrdWaves = 3;
-constexpr int kOrdBatch = 8 * kOrdWaves;
-
-template <bool kAct>
+// The same replay with one workgroup per scenario: kOrdWaves waves prepare the
+// ticks of the next batch (tick_order), eight each, while one more decides those
+// of the batch before it.
+template <bool kAct, int kOrdWaves>
 __global__ __launch_bounds__(64 * (kOrdWaves + 1)) void rebalance_ordered(CtlParams p) {
+  constexpr int kOrdBatch = 8 * kOrdWaves;  // at most 64: a lane per tick holds its vetoes
   __shared__ uint32_t s_recv[2][kOrdBatch * TRE_MAX_MODELS], s_don[2][kOrdBatch * TRE_MAX_MODELS];
   __shared__ uint32_t s_head[2][kOrdBatch];
   __shared__ unsigned long long s_z[kOrdWaves][64];
@@ -3386,16 +3384,21 @@ static int act_windows(const tre_events* ev, const tre_actuation* act, ActWindow
   return TRE_OK;
 }
 
-// Scenarios up to which each gets a workgroup of four waves (rebalance_ordered).
-// 1536 of them are on the chip at once (six a CU, by LDS and registers). Ordering
-// a tick costs an instruction stream per model, the folds hardly grow with the
-// models, so the line falls with them; measured, one wave a scenario / four, us
-// for 360 ticks: 8 models: 1024 scenarios 312 / 143, 1536 341 / 169, 2048 341 /
-// 276; under actuation 1536 413 / 255, 2048 414 / 429; 16 models: 2048 368 / 317;
-// 32 models: 768 398 / 317 (seldom moving 337 / 302), 1024 seldom moving 336 /
-// 361, 2048 433 / 658; 40 models: 256 405 / 360 (720 ticks 658 / 689), 512 408 /
-// 527; 64 models: 64 446 / 525, 2048 491 / 2359.
-static uint32_t ord_scenarios(int M, bool act) { return M <= 16 ? (act ? 1536 : 2048) : M <= 32 ? 768 : 0; }
+// Scenarios up to which each gets a workgroup (rebalance_ordered): of four waves
+// up to 32 models, six of them a CU by LDS and registers; above of eight, since
+// ordering a tick costs an instruction stream per model. The folds' cost hardly
+// grows with the models, so the line falls with them. Measured, one wave a
+// scenario / this, us for 360 ticks (240 where marked *, with many moves, as the
+// generator's workloads have them): 8 models: 1024 scenarios 312 / 143, 1536 341 /
+// 169, 2048 341 / 276; under actuation 1536 413 / 255, 2048 414 / 429; 16 models:
+// 2048 368 / 317; 24 models: 1024 374 / 307, 1536 407 / 416; 32 models: 768 398 /
+// 317 (seldom moving 337 / 302, *589 / 267), 1024 seldom moving 336 / 361; 33
+// models: 512 402 / 368 (*591 / 325), 768 401 / 542; 48 models: 256 444 / 303
+// (*553 / 261), 512 443 / 489; 64 models: 256 442 / 369 (seldom moving 371 / 368,
+// *576 / 286), 1 365 / 354 (seldom moving 323 / 350), 512 444 / 627.
+static uint32_t ord_scenarios(int M, bool act) {
+  return M <= 16 ? (act ? 1536 : 2048) : M <= 24 ? 1024 : M <= 32 ? 768 : M <= 40 ? 512 : 256;
+}
 
 static int launch_rebalance(const tre_events* ev, const tre_profile* prof, const double* vals,
                             const uint8_t* flags, const tre_scenario* sc, uint32_t n_sc,
@@ -3430,10 +3433,14 @@ static int launch_rebalance(const tre_events* ev, const tre_profile* prof, const
   const dim3 grid((unsigned)(((uint64_t)n_sc + 3) / 4)), block(256);
   LaunchTimer lt("rebalance", st);
   const bool ordered = n_sc <= ord_scenarios(c.M, aw != nullptr);
-  if (ordered && aw)
-    hipLaunchKernelGGL(rebalance_ordered<true>, dim3(n_sc), dim3(64 * (kOrdWaves + 1)), 0, st, c);
+  if (ordered && c.M > 32 && aw)
+    hipLaunchKernelGGL((rebalance_ordered<true, 7>), dim3(n_sc), dim3(64 * 8), 0, st, c);
+  else if (ordered && c.M > 32)
+    hipLaunchKernelGGL((rebalance_ordered<false, 7>), dim3(n_sc), dim3(64 * 8), 0, st, c);
+  else if (ordered && aw)
+    hipLaunchKernelGGL((rebalance_ordered<true, 3>), dim3(n_sc), dim3(64 * 4), 0, st, c);
   else if (ordered)
-    hipLaunchKernelGGL(rebalance_ordered<false>, dim3(n_sc), dim3(64 * (kOrdWaves + 1)), 0, st, c);
+    hipLaunchKernelGGL((rebalance_ordered<false, 3>), dim3(n_sc), dim3(64 * 4), 0, st, c);
   else if (aw)
     hipLaunchKernelGGL(rebalance<true>, grid, block, 0, st, c);
   else

@@ -84,8 +84,9 @@ def test_scenario_counts(lib, n_sc):
     P._check_set(lib, f"{n_sc} scenarios", w.trace_cfg(), [evs.trace(0)], w.profile_columns(1), sc)
 
 
-@pytest.mark.parametrize("M,n_sc,act", [(16, 1536, True), (16, 1537, True), (17, 768, False), (17, 769, True), (32, 768, True),
-                                        (32, 3, False), (33, 1, False), (33, 3, True)])
+@pytest.mark.parametrize("M,n_sc,act", [(16, 1536, True), (16, 1537, True), (17, 1024, False), (24, 1025, True), (25, 768, True),
+                                        (32, 769, False), (33, 1, False), (33, 512, True), (40, 513, False), (41, 256, True),
+                                        (41, 257, False), (64, 3, True), (64, 256, False)])
 def test_replay_rule(lib, M, n_sc, act):
     """The models and scenarios at which the replay changes kernels, every window
     a tick."""
