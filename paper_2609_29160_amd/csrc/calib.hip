@@ -1624,10 +1624,13 @@ static int launch_fit(const tre_events* ev, const tre_slo* slo, const double* ts
 
 // Few long traces go by records at once: one workgroup per trace leaves most
 // of the chip idle. The stream takes 2.4 ns a row of the longest trace (up to
-// two workgroups a CU), the records 18 ps a row of every trace plus a 16-byte
-// record per id (16 traces of 6.1 M rows: 14651 / 1770 us), so the line lies
-// near 130 traces; below 2^17 rows the records' three launches show, and ids
-// far apart would cost more records than rows.
+// two workgroups a CU), the records about 20 ps a row of every trace plus a
+// 16-byte record per id (stream / records in us: 16 traces of 6.1 M rows 14651 /
+// 1770, 96 of 0.9 M 11848 / 2037, 96 of 22,000 111 / 80, 400 of 0.28 M 4912 /
+// 2754). The two meet above 400 traces; the rule stops at 96, as far as its
+// memory of a record per id and trace was meant to go. Below 2^17 rows the
+// records' three launches show, and ids far apart would cost more records than
+// rows.
 constexpr int64_t kRecordsTraces = 96, kRecordsRows = 1 << 17;
 static bool records_first(const tre_events* ev, int64_t maxlen, uint32_t req_cap) {
   return (int64_t)ev->n_traces <= kRecordsTraces && maxlen >= kRecordsRows && (int64_t)req_cap <= maxlen;
