@@ -3184,7 +3184,8 @@ struct SegPlan {
 //   624 / 633); above 16 models 0.85 M (0.72 M 1245 / 644, 0.89 M 634 / 701, 1.08 M
 //   521 / 615), 1.0 M up to 160 traces (0.93 M 460 / 352, 1.06 M 64 / 77). To 384
 //   traces, whose workgroups take two rounds: 2.0 M (1.68 M 1123 / 922, 2.57 M 221
-//   / 237), above 16 models 1.5 M (0.82 M 2079 / 656, 1.60 M 587 / 719). To 768
+//   / 237), above 16 models 1.5 M (0.82 M 2079 / 656, 1.60 M 587 / 719), 1.75 M with
+//   outputs (1.69 M 512 / 416, 2.05 M 530 / 603). To 768
 //   (8-wave workgroups): 1.0 M (0.97 M 960 / 714, 0.96 M 805 / 650, 1.14 M 547 / 688,
 //   1.7 M 418 / 568), 1.2 M in long calls with per-cell outputs (1.14 M 423 / 339,
 //   1.05 M under actuation 1712 / 1421, without outputs 1121 / 1390).
@@ -3199,7 +3200,7 @@ bool seg_pays(const tre_events* ev, bool stage, bool cells) {
   const double chunk_rows = (double)C * (double)ev->n_events / (double)nW;
   if (stage) return chunk_rows <= 1.5 * (kStreamWaves * 64 * kStreamEPT) * (double)T;
   if (T <= 256) return chunk_rows <= (wide ? (T <= kFew ? 1.0e6 : 0.85e6) : cells ? 1.5e6 : 1.1e6);
-  if (T <= 384) return chunk_rows <= (wide ? 1.5e6 : 2.0e6);
+  if (T <= 384) return chunk_rows <= (wide ? (cells ? 1.75e6 : 1.5e6) : 2.0e6);
   return chunk_rows <= (cells && nW >= 1000 ? 1.2e6 : 1.0e6);
 }
 
